@@ -129,6 +129,22 @@ struct StepStreams {
     }
 };
 
+// Captured step graphs of a run or group, one per kind of batch.
+struct Batch {
+    int twos, ones;                   // two-step passes, then single steps
+    int steps() const { return 2 * twos + ones; }
+    int flips() const { return twos + ones; }
+};
+struct GraphCache {
+    struct Item { Batch b; hipGraphExec_t x; };
+    std::vector<Item> items;
+    bool failed = false;              // the runtime refused a capture: launch eagerly
+    void drop() {
+        for (auto &i : items) (void)hipGraphExecDestroy(i.x);
+        items.clear();
+    }
+};
+
 }  // namespace
 
 struct lbm_run {
@@ -144,7 +160,8 @@ struct lbm_run {
     RunDev *dd = nullptr;
     RunDev **dptr = nullptr;
     int *dprefix = nullptr;   // [NCLS][2] prefix arrays of the single-run launch set
-    int nblocks[NCLS] = {0, 0, 0, 0};
+    int nblocks[NCLS] = {};
+    int core_rows = 0;        // rows of a two-step tile; 0: single steps only
     const LatticeInfo *lat = &LATTICE_D2Q37;   // velocity stencil
     const KernelSet *ks = &k37::kernels;       // its kernels
     double fbar[NQ_MAX];
@@ -154,12 +171,7 @@ struct lbm_run {
     lbm_launch launch{64, 4, 32, 2, -1};
     int64_t steps = 0;
     DeviceMem mem;
-    hipGraphExec_t graph = nullptr;
-    int graph_G = 0;
-    int graph_tx = 0;
-    int graph_ov = 0;
-    int graph_split = -1;
-    bool graph_failed = false;
+    GraphCache graphs;
     int prof = 0;                     // 0 off, 1 classes in order, 2 bulk kernel in the normal schedule,
                                       // 3 as 2 on the first step of each batch only
     struct Ev { hipEvent_t a, b; int cls; };
@@ -185,9 +197,8 @@ struct lbm_group {
     int storage = -1;
     const KernelSet *ks = nullptr;    // stencil of the members (set by the first member)
     lbm_launch launch{64, 4, 32, 2, -1};
-    hipGraphExec_t graph = nullptr;   // graph_G batched steps of the current membership
-    int graph_G = 0;
-    bool graph_failed = false;
+    GraphCache graphs;                // batched steps of the current membership
+    int core_rows = 0;                // rows of a two-step tile; 0: single steps only
     RunDev **druns = nullptr;
     int *dprefix = nullptr;
     long long *dlimits = nullptr;
@@ -196,7 +207,7 @@ struct lbm_group {
     int *hflags = nullptr;            // pinned
     hipEvent_t upload_done = nullptr;
     bool upload_pending = false;
-    int blocks[NCLS] = {0, 0, 0, 0};
+    int blocks[NCLS] = {};
     size_t cap = 0;
     int poison = 0;                   // some member has the NaN canary on
     bool ranges = false;              // some member asks for roctx ranges around the steps
@@ -205,6 +216,46 @@ struct lbm_group {
 namespace {
 
 // ---- geometry ------------------------------------------------------------------------------
+// Interior sides from which a run can take its steps in pairs (below, too little of a two-step tile
+// is its own), and whether a set of runs with this many interior and frame nodes in all does.  A
+// pair reads and writes the interior once in place of twice, but its boundary work no longer hides
+// beside the streaming tiles.  us per step, single / paired: FP64 D2Q37 512^2 + 32 cells NRBC 68.9 /
+// 66.0, 768^2 ZG 101.3 / 89.5, 1024^2 NRBC 172.4 / 151.7, 4096^2 2214 / 1627; D2Q17 768^2 51.8 /
+// 50.5, D2Q9 768^2 30.8 / 28.1 (512^2 35.0 / 36.9 and 23.0 / 22.3).  FP32, whose tiles are bound by
+// arithmetic: 1024^2 without a layer 72.2 / 63.7, with 32 cells 96.2 / 100.2, 2048^2 with 32 cells
+// 285 / 236.  FP16 never: half the bytes to save, and 48-column stores in place of whole lines
+// (1024^2 57.6 / 113.9).
+constexpr int TWO_STEP_MIN_SIDE = 96;
+bool two_steps_pay(int storage, long long interior, long long frame) {
+    return storage == ST_F64   ? interior >= 400000 + frame
+           : storage == ST_F32 ? interior >= 800000 + 5 * frame
+                               : false;
+}
+
+// Geometry of the two-step passes: strips of the interior off its outer `reach` layers, the shell,
+// and the bands (see RunDev).
+void setup_two_steps(lbm_run *h, RunDev &R) {
+    const int reach = reach_of(*h->lat), nq = h->lat->q, deep = 2 * reach;
+    const int w = R.fx1 - R.fx0, hgt = R.fy1 - R.fy0;
+    R.core_strips = 0;
+    R.shell_n = 0;
+    R.msize = 0;
+    if (h->desc.layout != 0) return;   // the two-step tiles address rows of the row layout
+    if (h->desc.storage == ST_F16) return;
+    if (w < TWO_STEP_MIN_SIDE || hgt < TWO_STEP_MIN_SIDE) return;
+    if ((long long)(2 * reach + 1) * R.pitch * 8 >= (1LL << 31)) return;   // 32-bit offsets in a tile's rows
+    R.bL = R.gxm + deep; R.bR = R.gxp + deep;
+    R.bB = R.gym + deep; R.bT = R.gyp + deep;
+    R.m_row = (int)round_up(R.Nx, 64);
+    R.l_row = (int)round_up(R.bL + R.bR, 16);
+    R.l_first = (long long)nq * R.m_row * (R.bB + R.bT);
+    R.msize = R.l_first + (long long)nq * R.l_row * (R.Ny - R.gym - R.gyp);
+    if (R.msize >= (1LL << 32)) { R.msize = 0; return; }   // the bands use 32-bit element indices
+    const int es = (int)elem_size(h->desc.storage), out = core_out(reach, es);
+    R.core_strips = (R.fx1 - reach - core_x0(R.fx0, reach, es) + out - 1) / out;
+    R.shell_n = w * hgt - (w - 2 * reach) * (hgt - 2 * reach);
+}
+
 lbm_status setup_geometry(lbm_run *h, RunDev &R) {
     const lbm_desc &d = h->desc;
     R.Wxm = h->pml[XMIN] ? h->W : 0;
@@ -287,6 +338,7 @@ lbm_status setup_geometry(lbm_run *h, RunDev &R) {
         R.plane = round_up(row * R.Ny, 64);
         R.fsize = (long long)nq * R.plane;
     }
+    setup_two_steps(h, R);
     R.qplane = round_up(std::max(R.ann0 + R.ann_n, 1), 64);
     R.rplane = round_up(std::max(R.ring_n, 1), 64);
     // the bulk kernel addresses a tile (at most 4 rows) with a 32-bit byte offset from a
@@ -327,10 +379,10 @@ void fill_constants(lbm_run *h, RunDev &R) {
     const double k1 = 1.0 - 0.5 * b0 - 2.0 * th0;
     const double k2a = o4 ? 0.5 - 0.25 * b0 - 1.5 * th0 : 0.5;
     const double k2s = o4 ? 0.5 * th0 - 0.25 * th0 * b0 - th0 * th0 : 0.5 * th0;
-    double E0[NSHELL_MAX];
+    double Es[NSHELL_MAX];
     for (int s = 0; s < lt.nshell; ++s) {
         double sv = lt.r * lt.r * lt.shell_e2[s];
-        E0[s] = k0 + k2s * sv + (o4 ? 0.125 * th0 * th0 * sv * sv : 0.0);
+        Es[s] = k0 + k2s * sv + (o4 ? 0.125 * th0 * th0 * sv * sv : 0.0);
         R.E2_0[s] = k2a + (o4 ? 0.25 * th0 * sv : 0.0);
         R.O1_0[s] = o2 ? 1.0 : k1 + 0.5 * th0 * sv;   // eq. feq-2: the odd part is a itself
     }
@@ -339,10 +391,30 @@ void fill_constants(lbm_run *h, RunDev &R) {
     for (int p = 0; p < lt.npair; ++p) {
         int sh = lt.psh[p];
         double a0 = lt.pex[p] * R.r0x + lt.pey[p] * R.r0y;
-        R.H0e[p] = E0[sh] + R.E2_0[sh] * a0 * a0 + (o4 ? a0 * a0 * a0 * a0 / 24.0 : 0.0);
+        R.H0e[p] = Es[sh] + R.E2_0[sh] * a0 * a0 + (o4 ? a0 * a0 * a0 * a0 / 24.0 : 0.0);
         R.H0o[p] = o2 ? a0 : a0 * (R.O1_0[sh] + a0 * a0 / 6.0);
         h->fbar[1 + 2 * p] = lt.shell_w[sh] * d.rho0 * (R.H0e[p] + R.H0o[p]);
         h->fbar[2 + 2 * p] = lt.shell_w[sh] * d.rho0 * (R.H0e[p] - R.H0o[p]);
+    }
+    const double x = R.r0x, y = R.r0y, r2 = lt.r * lt.r;
+    R.xx0 = x * x; R.xy0 = x * y; R.yy0 = y * y; R.k2a0 = k2a; R.k10 = k1;
+    double *e = R.eq0;
+    for (int c = 0; c < NEQ; ++c) e[c] = 0.0;
+    e[E0] = k0;
+    e[E1] = r2 * k2s;
+    e[BXX] = k2a * x * x; e[BXY] = 2.0 * k2a * x * y; e[BYY] = k2a * y * y;
+    if (o4) {
+        e[E2] = r2 * r2 * th0 * th0 / 8.0;
+        e[TXX] = 0.25 * r2 * th0 * x * x; e[TXY] = 0.5 * r2 * th0 * x * y; e[TYY] = 0.25 * r2 * th0 * y * y;
+        e[Q40] = x * x * x * x / 24.0; e[Q31] = x * x * x * y / 6.0; e[Q22] = x * x * y * y / 4.0;
+        e[Q13] = x * y * y * y / 6.0; e[Q04] = y * y * y * y / 24.0;
+    }
+    if (o2) {   // eq. feq-2: the odd part is a itself
+        e[LX] = x; e[LY] = y;
+    } else {
+        e[LX] = k1 * x; e[LY] = k1 * y;
+        e[MX] = 0.5 * r2 * th0 * x; e[MY] = 0.5 * r2 * th0 * y;
+        e[C30] = x * x * x / 6.0; e[C21] = x * x * y / 2.0; e[C12] = x * y * y / 2.0; e[C03] = y * y * y / 6.0;
     }
     R.omega_f = (float)R.omega; R.rho0_f = (float)R.rho0; R.u0x_f = (float)R.u0x;
     R.u0y_f = (float)R.u0y; R.th0_f = (float)R.th0; R.b0_f = (float)R.b0;
@@ -359,7 +431,7 @@ void set_scale(RunDev &R, double s) {
 }
 
 size_t footprint_of(const RunDev &R, int storage, int nq) {
-    size_t b = 2 * (size_t)R.fsize * elem_size(storage);
+    size_t b = 2 * (size_t)R.fsize * elem_size(storage) + (size_t)R.msize * elem_size(storage);
     if (R.has_q) b += (size_t)nq * R.qplane * compute_size(storage);
     b += 2 * 4 * (size_t)R.qplane * sizeof(double);
     if (R.ring_n > 0) b += (size_t)nq * R.rplane * compute_size(storage);
@@ -372,7 +444,8 @@ size_t footprint_of(const RunDev &R, int storage, int nq) {
     return b;
 }
 
-void compute_blocks(const RunDev &R, int tx, int nb[NCLS]) {
+// Blocks of a run per launch class; rows: height of the two-step tiles (0: none).
+void compute_blocks(const RunDev &R, int tx, int rows, int reach, int nb[NCLS]) {
     int k = tx_index(tx);
     nb[CLS_BULK] = R.tiles_x[k] * R.tiles_y[k];
     const int fb = frame_block_count(R.ann_n);
@@ -380,10 +453,51 @@ void compute_blocks(const RunDev &R, int tx, int nb[NCLS]) {
     nb[CLS_FRAME] = rb + fb;
     nb[CLS_A] = rb + (R.has_q ? fb : 0);
     nb[CLS_TGT] = R.tgt_pre ? rb : 0;
+    const bool two = rows > 0 && R.core_strips > 0;
+    const int hc = R.fy1 - R.fy0 - 2 * reach;
+    nb[CLS_CORE] = two ? R.core_strips * ((hc + rows - 1) / rows) : 0;
+    nb[CLS_FRAME2] = two ? rb + fb + (R.shell_n + FRAME_BLOCK - 1) / FRAME_BLOCK : 0;
+}
+
+// Height of the two-step tiles of a set of runs: a tile of H rows forms H + 2 reach rows of the
+// level between, CORE_R per turn, and the device holds `slots` tiles at a time, so the time goes
+// as ceil(tiles / slots) times a tile's turns and half a turn to start; the H with the least.  0 if
+// the set takes single steps.
+int choose_core_rows(lbm_run *const *runs, size_t n) {
+    if (n == 0) return 0;
+    const LatticeInfo &lt = *runs[0]->lat;
+    const int reach = reach_of(lt);
+    int tallest = 0;
+    long long interior = 0, frame = 0;
+    for (size_t k = 0; k < n; ++k) {
+        const RunDev &R = runs[k]->hd;
+        if (R.core_strips == 0 || !R.M) return 0;
+        interior += (long long)(R.fx1 - R.fx0) * (R.fy1 - R.fy0);
+        frame += R.frame_n;
+        tallest = std::max(tallest, R.fy1 - R.fy0 - 2 * reach);
+    }
+    if (!two_steps_pay(runs[0]->desc.storage, interior, frame)) return 0;
+    const long long slots = 256 * (long long)core_tiles_per_cu(lt, (int)elem_size(runs[0]->desc.storage));
+    long long best = -1;
+    int best_h = 0;
+    for (int c = 1; c <= tallest; ++c) {          // c tiles up the tallest run
+        const int H = (tallest + c - 1) / c;
+        if (H < CORE_R && best_h) break;
+        long long tiles = 0;
+        for (size_t k = 0; k < n; ++k) {
+            const RunDev &R = runs[k]->hd;
+            tiles += (long long)R.core_strips * ((R.fy1 - R.fy0 - 2 * reach + H - 1) / H);
+        }
+        const int turns = (H + 2 * reach + CORE_R - 1) / CORE_R;
+        const long long cost = ((tiles + slots - 1) / slots) * (2 * turns + 1);
+        if (best < 0 || cost < best) { best = cost; best_h = H; }
+    }
+    return best_h;
 }
 
 lbm_status upload_prefix(lbm_run *h) {
-    compute_blocks(h->hd, h->launch.bulk_tx, h->nblocks);
+    h->core_rows = choose_core_rows(&h, 1);
+    compute_blocks(h->hd, h->launch.bulk_tx, h->core_rows, reach_of(*h->lat), h->nblocks);
     int pre[2 * NCLS];
     for (int c = 0; c < NCLS; ++c) { pre[2 * c] = 0; pre[2 * c + 1] = h->nblocks[c]; }
     HIP_TRY(hipMemcpyAsync(h->dprefix, pre, sizeof pre, hipMemcpyHostToDevice, h->stream));
@@ -401,6 +515,7 @@ LaunchSet single_set(lbm_run *h) {
     }
     L.poison = (h->debug & LBM_DEBUG_POISON) ? 1 : 0;
     L.split = h->launch.split;
+    L.core_rows = h->launch.overlap == 2 && !h->prof && !L.poison ? h->core_rows : 0;
     L.nruns = 1;
     return L;
 }
@@ -447,14 +562,14 @@ hipEvent_t take_event(lbm_run *h) {
 // bulk kernel) and the frame kernel (class 1); mode 3 does so on every fourth sub-step only.  The
 // events of the kernels are attached to their dispatch (their own start and end); phase A in
 // mode 1 is bracketed by event records.
-lbm_status enqueue_substep(const LaunchSet &L, int storage, int tx, int ks, hipStream_t s,
+lbm_status enqueue_substep(const LaunchSet &L, int storage, int tx, Sub ks, hipStream_t s,
                            StepStreams *ss, bool fused, lbm_run *prof) {
     const bool has_a = L.blocks[CLS_A] > 0;
     const bool has_f = L.blocks[CLS_FRAME] > 0;
     const bool has_b = L.blocks[CLS_BULK] > 0;
     if (L.poison) HIP_TRY(L.ks->poison(L, storage, ks, s));
     const int pm = prof ? prof->prof : 0;
-    const int mode = pm == 3 ? ((ks & 3) == 0 ? 2 : 0) : pm;
+    const int mode = pm == 3 ? ((ks.steps & 3) == 0 ? 2 : 0) : pm;
     hipEvent_t ev[6] = {};
     if (mode) {
         harvest_events(prof, false);
@@ -497,36 +612,35 @@ lbm_status enqueue_substep(const LaunchSet &L, int storage, int tx, int ks, hipS
     return LBM_OK;
 }
 
-// A batch of nb sub-steps, then one launch that advances every run's step counter and buffer
-// parity by the sub-steps it was active for.
-lbm_status enqueue_batch(const LaunchSet &L, int storage, int tx, int nb, hipStream_t s,
+// A batch: its two-step passes, its single steps, then one launch that advances every run's step
+// counter and buffer parity by the sub-steps it was active for.
+lbm_status enqueue_batch(const LaunchSet &L, int storage, int tx, Batch b, hipStream_t s,
                          StepStreams *ss, bool fused, lbm_run *prof) {
-    for (int ks = 0; ks < nb; ++ks) {
+    Sub ks{0, 0};
+    for (int k = 0; k < b.twos; ++k, ks.steps += 2, ++ks.flips)
+        HIP_TRY(L.ks->two_steps(L, storage, ks, s));
+    for (int k = 0; k < b.ones; ++k, ++ks.steps, ++ks.flips) {
         lbm_status st = enqueue_substep(L, storage, tx, ks, s, ss, fused, prof);
         if (st != LBM_OK) return st;
     }
-    HIP_TRY(L.ks->advance(L, nb, s));
+    HIP_TRY(L.ks->advance(L, b.steps(), b.flips(), s));
     return LBM_OK;
 }
 
 // Sub-steps per eager batch when graphs are off.
 constexpr int EAGER_BATCH = 32;
+// Fewest steps between two runs' stops that a group takes in pairs.
+constexpr int64_t PAIRED_STRETCH = 8;
 
-void drop_graph(lbm_run *h) {
-    if (h->graph) (void)hipGraphExecDestroy(h->graph);
-    h->graph = nullptr;
-    h->graph_G = 0;
-}
-
-// Capture G in-order steps of a launch set on stream s into an executable graph; nullptr if the
-// runtime refuses (the caller then launches eagerly).
-hipGraphExec_t capture_steps(const LaunchSet &L, int storage, int tx, bool fused, hipStream_t s, int G) {
+// Capture a batch of a launch set on stream s into an executable graph; nullptr if the runtime
+// refuses (the caller then launches eagerly).
+hipGraphExec_t capture_batch(const LaunchSet &L, int storage, int tx, bool fused, hipStream_t s, Batch b) {
     hipGraph_t g = nullptr;
     if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
-    lbm_status st = enqueue_batch(L, storage, tx, G, s, nullptr, fused, nullptr);
+    lbm_status st = enqueue_batch(L, storage, tx, b, s, nullptr, fused, nullptr);
     hipError_t e = hipStreamEndCapture(s, &g);
     if (st != LBM_OK || e != hipSuccess || !g) {
         (void)hipGetLastError();
@@ -543,20 +657,63 @@ hipGraphExec_t capture_steps(const LaunchSet &L, int storage, int tx, bool fused
     return x;
 }
 
-lbm_status build_graph(lbm_run *h, int G) {
-    drop_graph(h);
-    h->graph = capture_steps(single_set(h), h->desc.storage, h->launch.bulk_tx, h->launch.overlap == 2,
-                             h->stream, G);
-    if (!h->graph) {
-        h->graph_failed = true;
+// The step launcher of a run or group: batches in order, a batch of `whole` steps (0: never; one
+// less in a closing batch of odd length) as a replay of its captured graph, any other eagerly.
+struct Stepper {
+    const LaunchSet &L;
+    int storage, tx;
+    hipStream_t s;
+    StepStreams *ss;
+    bool fused;
+    lbm_run *prof;
+    GraphCache &graphs;
+    int whole;
+
+    lbm_status run(Batch b) {
+        if (b.steps() == 0) return LBM_OK;
+        if (whole > 0 && b.steps() + 1 >= whole && !graphs.failed) {
+            for (auto &i : graphs.items)
+                if (i.b.twos == b.twos && i.b.ones == b.ones) {
+                    HIP_TRY(hipGraphLaunch(i.x, s));
+                    return LBM_OK;
+                }
+            if (hipGraphExec_t x = capture_batch(L, storage, tx, fused, s, b)) {
+                graphs.items.push_back({b, x});
+                HIP_TRY(hipGraphLaunch(x, s));
+                return LBM_OK;
+            }
+            graphs.failed = true;
+        }
+        return enqueue_batch(L, storage, tx, b, s, ss, fused, prof);
+    }
+
+    // `n` single steps, in batches of B
+    lbm_status singles(int64_t n, int B) {
+        while (n > 0) {
+            const int b = (int)std::min<int64_t>(n, B);
+            lbm_status st = run({0, b});
+            if (st != LBM_OK) return st;
+            n -= b;
+        }
         return LBM_OK;
     }
-    h->graph_G = G;
-    h->graph_tx = h->launch.bulk_tx;
-    h->graph_ov = h->launch.overlap;
-    h->graph_split = h->launch.split;
-    return LBM_OK;
-}
+
+    // `n` steps at whose end runs may stop: in pairs, the last one or two singly, so that both
+    // population buffers then hold consecutive levels (the moments re-pull the level before)
+    lbm_status pairs(int64_t n, int B) {
+        const int tail = 2 - (int)(n & 1);
+        const int64_t last = std::min<int64_t>(n, B - (n & 1));   // the closing batch
+        int64_t twos = (n - last) / 2;
+        const Batch end{(int)((last - tail) / 2), tail};
+        while (twos > 0) {
+            const int b = (int)std::min<int64_t>(twos, B / 2);
+            lbm_status st = run({b, 0});
+            if (st != LBM_OK) return st;
+            twos -= b;
+        }
+        return run(end);
+    }
+};
 
 bool finite_all(const double *a, size_t n) {
     for (size_t i = 0; i < n; ++i)
@@ -673,7 +830,7 @@ lbm_status lbm_set_debug(lbm_handle h, unsigned flags) {
     if (flags & ~(unsigned)(LBM_DEBUG_POISON | LBM_DEBUG_RANGES)) return fail(LBM_ERR_ARG, "unknown debug flag");
     if (h->debug == flags) return LBM_OK;
     h->debug = flags;
-    drop_graph(h);                       // captured steps are recaptured with the new flags
+    h->graphs.drop();                    // captured steps are recaptured with the new flags
     if (h->group) h->group->dirty = true;
     return LBM_OK;
 }
@@ -744,6 +901,8 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
     }
     R.Q = R.has_q ? h->mem.get((size_t)h->lat->q * R.qplane * cs) : nullptr;
     R.G = R.ring_n > 0 ? h->mem.get((size_t)h->lat->q * R.rplane * cs) : nullptr;
+    // without the bands the run takes single steps
+    R.M = R.msize > 0 ? h->mem.get((size_t)R.msize * es) : nullptr;
     const bool need_p = R.tgt_pre && R.ring_n > 0;
     R.P = need_p ? (double *)h->mem.get(4 * (size_t)R.rplane * sizeof(double)) : nullptr;
     h->dd = (RunDev *)h->mem.get(sizeof(RunDev));
@@ -817,35 +976,17 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
 // Enqueue n > 0 steps of a run that is not in a group.
 lbm_status enqueue_steps(lbm_handle h, int64_t n) {
     HIP_TRY(h->ks->set_limit(h->dd, (long long)(h->steps + n), h->stream));
-    LaunchSet L = single_set(h);
-    int64_t left = n;
+    const LaunchSet L = single_set(h);
     const int G = h->launch.graph_steps;
     // Overlapped steps launch eagerly (stream capture stays single-stream); in-order steps
     // replay captured graphs of G steps.  The side stream is created on first use.
     if (h->launch.overlap == 1 && !h->desc.stream && !h->ss.ok) HIP_TRY(h->ss.create());
     const bool overlap = h->launch.overlap == 1 && h->ss.ok;
-    const bool fused = h->launch.overlap == 2;
-    if (!h->prof && !overlap && G > 0 && !h->graph_failed && n >= G) {
-        if (!h->graph || h->graph_G != G || h->graph_tx != h->launch.bulk_tx ||
-            h->graph_ov != h->launch.overlap || h->graph_split != h->launch.split) {
-            lbm_status st = build_graph(h, G);
-            if (st != LBM_OK) return st;
-        }
-        if (h->graph) {
-            while (left >= G) {
-                HIP_TRY(hipGraphLaunch(h->graph, h->stream));
-                left -= G;
-            }
-        }
-    }
+    Stepper st{L, h->desc.storage, h->launch.bulk_tx, h->stream, overlap ? &h->ss : nullptr,
+               h->launch.overlap == 2, h->prof ? h : nullptr, h->graphs, h->prof || overlap ? 0 : G};
     const int B = G > 0 ? G : EAGER_BATCH;
-    while (left > 0) {
-        const int nb = (int)std::min<int64_t>(left, B);
-        lbm_status st = enqueue_batch(L, h->desc.storage, h->launch.bulk_tx, nb, h->stream,
-                                      overlap ? &h->ss : nullptr, fused, h->prof ? h : nullptr);
-        if (st != LBM_OK) return st;
-        left -= nb;
-    }
+    lbm_status rc = L.core_rows > 0 ? st.pairs(n, B) : st.singles(n, B);
+    if (rc != LBM_OK) return rc;
     h->steps += n;
     return LBM_OK;
 }
@@ -1056,6 +1197,7 @@ lbm_status lbm_set_launch(lbm_handle h, const lbm_launch *cfg) {
     if (cfg->overlap < 0 || cfg->overlap > 2) return fail(LBM_ERR_ARG, "overlap must be 0, 1 or 2");
     if (cfg->split < -1 || cfg->split > 8) return fail(LBM_ERR_ARG, "split must be -1 or 0..8");
     if (h->group) return fail(LBM_ERR_STATE, "run is in a group");
+    h->graphs.drop();   // step graphs hold the old configuration
     h->launch = *cfg;
     if (h->inited) return upload_prefix(h);
     return LBM_OK;
@@ -1090,7 +1232,7 @@ void lbm_destroy(lbm_handle h) {
     if (!h) return;
     if (h->group) lbm_group_remove(h->group, h);
     if (h->inited) (void)hipStreamSynchronize(h->stream);
-    drop_graph(h);
+    h->graphs.drop();
     for (auto &ev : h->pending) { (void)hipEventDestroy(ev.a); (void)hipEventDestroy(ev.b); }
     for (auto e : h->pool) (void)hipEventDestroy(e);
     h->mem.release_all();
@@ -1338,16 +1480,10 @@ lbm_status lbm_group_synchronize(lbm_group_handle g) {
     return LBM_OK;
 }
 
-static void group_drop_graph(lbm_group *g) {
-    if (g->graph) (void)hipGraphExecDestroy(g->graph);
-    g->graph = nullptr;
-    g->graph_G = 0;
-}
-
 static lbm_status group_rebuild(lbm_group *g) {
     const size_t n = g->members.size();
     HIP_TRY(hipStreamSynchronize(g->stream));
-    group_drop_graph(g);
+    g->graphs.drop();
     if (n > g->cap) {
         g->mem.put(g->druns); g->mem.put(g->dprefix); g->mem.put(g->dlimits); g->mem.put(g->dflags);
         size_t cap = std::max<size_t>(n, 64);
@@ -1361,12 +1497,13 @@ static lbm_status group_rebuild(lbm_group *g) {
     }
     std::vector<RunDev *> ptrs(n);
     std::vector<int> pre(NCLS * (g->cap + 1), 0);
-    int tot[NCLS] = {0, 0, 0, 0};
+    int tot[NCLS] = {};
+    g->core_rows = choose_core_rows(g->members.data(), n);
     for (size_t k = 0; k < n; ++k) {
         lbm_run *h = g->members[k];
         ptrs[k] = h->dd;
         int nb[NCLS];
-        compute_blocks(h->hd, g->launch.bulk_tx, nb);
+        compute_blocks(h->hd, g->launch.bulk_tx, g->core_rows, reach_of(*h->lat), nb);
         for (int c = 0; c < NCLS; ++c) { pre[c * (g->cap + 1) + k] = tot[c]; tot[c] += nb[c]; }
     }
     for (int c = 0; c < NCLS; ++c) pre[c * (g->cap + 1) + n] = tot[c];
@@ -1413,29 +1550,33 @@ lbm_status lbm_group_step(lbm_group_handle g, const int64_t *steps, int64_t nste
     L.nruns = (int)n;
     L.poison = g->poison;
     L.split = g->launch.split;
+    L.core_rows = g->launch.overlap == 2 && !g->poison ? g->core_rows : 0;
     // Runs past their own count skip every kernel, so whole graphs of G batched steps serve any
     // mix of counts; the remainder is launched eagerly.
-    int64_t left = K;
-    const int G = g->launch.graph_steps;
-    if (G > 0 && !g->graph_failed && K >= G) {
-        if (!g->graph || g->graph_G != G) {
-            group_drop_graph(g);
-            g->graph = capture_steps(L, g->storage, g->launch.bulk_tx, g->launch.overlap == 2, g->stream, G);
-            if (g->graph) g->graph_G = G;
-            else g->graph_failed = true;
+    const int G = g->launch.graph_steps, B = G > 0 ? G : EAGER_BATCH;
+    Stepper st{L, g->storage, g->launch.bulk_tx, g->stream, nullptr, g->launch.overlap == 2, nullptr, g->graphs, G};
+    lbm_status rc = LBM_OK;
+    if (L.core_rows > 0) {
+        // a run stops after a single step: pairs up to each distinct count, except that the last
+        // stretches between counts closer than PAIRED_STRETCH go singly together
+        std::vector<int64_t> stops;
+        for (size_t k = 0; k < n; ++k) stops.push_back(steps ? steps[k] : nsteps);
+        std::sort(stops.begin(), stops.end());
+        int64_t at = 0, singles = 0;
+        for (int64_t c : stops) {
+            if (c <= at + singles) continue;
+            const int64_t stretch = c - at - singles;
+            if (stretch < PAIRED_STRETCH) { singles += stretch; continue; }
+            if ((rc = st.singles(singles, B)) != LBM_OK) return rc;
+            if ((rc = st.pairs(stretch, B)) != LBM_OK) return rc;
+            at = c;
+            singles = 0;
         }
-        if (g->graph) {
-            for (; left >= G; left -= G) HIP_TRY(hipGraphLaunch(g->graph, g->stream));
-        }
+        rc = st.singles(singles, B);
+    } else {
+        rc = st.singles(K, B);
     }
-    const int B = G > 0 ? G : EAGER_BATCH;
-    while (left > 0) {
-        const int nb = (int)std::min<int64_t>(left, B);
-        lbm_status st = enqueue_batch(L, g->storage, g->launch.bulk_tx, nb, g->stream, nullptr,
-                                      g->launch.overlap == 2, nullptr);
-        if (st != LBM_OK) return st;
-        left -= nb;
-    }
+    if (rc != LBM_OK) return rc;
     for (size_t k = 0; k < n; ++k) g->members[k]->steps += steps ? steps[k] : nsteps;
     return LBM_OK;
 }
@@ -1471,7 +1612,7 @@ lbm_status lbm_group_set_launch(lbm_group_handle g, const lbm_launch *cfg) {
     if (cfg->split < -1 || cfg->split > 8) return fail(LBM_ERR_ARG, "split must be -1 or 0..8");
     HIP_TRY(hipStreamSynchronize(g->stream));
     g->launch = *cfg;
-    g->graph_failed = false;
+    g->graphs.failed = false;
     g->dirty = true;   // block counts depend on the tile width; graphs are recaptured
     return LBM_OK;
 }
@@ -1555,7 +1696,7 @@ void lbm_group_destroy(lbm_group_handle g) {
         h->group = nullptr;
         h->stream = h->own_stream ? h->own_stream : (hipStream_t)h->desc.stream;
     }
-    group_drop_graph(g);
+    g->graphs.drop();
     g->mem.release_all();
     if (g->hlimits) (void)hipHostFree(g->hlimits);
     if (g->hflags) (void)hipHostFree(g->hflags);

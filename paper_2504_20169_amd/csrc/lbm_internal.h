@@ -49,8 +49,17 @@ struct alignas(256) RunDev {
     int axm, axp, aym, ayp;   // depths of the frame's annulus off the ring
     int ann0, ann_n;          // first frame index and count of the frame nodes off the ring
     int tiles_x[3], tiles_y[3];   // bulk tiles for tile widths 64, 128, 256
+    // two-step passes (core_strips = 0: the run takes single steps only).  The bands hold the level
+    // between of the frame and of the interior within 2 reach of it: a row band (bT rows below the
+    // top edge, then bB above the bottom one, every column) and a column band (bR columns, then bL,
+    // the rows off the frame's y strips), both with the q population rows of a row adjacent.
+    int core_strips, shell_n;     // strips of the two-step tiles; nodes of the shell
+    int bL, bR, bB, bT;
+    int m_row, l_row;             // elements of a population row of the row and the column band
+    long long l_first, msize;     // first element of the column band; elements of both
     // state
     void *f[2];
+    void *M;                  // bands of the two-step passes (or NULL)
     void *Q;                  // [q][qplane] in the compute type
     double *U[2];             // [4][qplane]: rho, ux, uy, T (absolute values)
     void *G;                  // [q][rplane] compute type: post-boundary populations of the ring
@@ -61,6 +70,7 @@ struct alignas(256) RunDev {
     // constants (double and float copies)
     double omega, rho0, u0x, u0y, T0, th0, b0, r0x, r0y, sigma_max, inv_W2, scale, inv_scale;
     double H0rest, H0e[NPAIR_MAX], H0o[NPAIR_MAX], E2_0[NSHELL_MAX], O1_0[NSHELL_MAX];
+    double xx0, xy0, yy0, k2a0, k10, eq0[NEQ];   // FP64 storage: the mean state's polynomial coefficients over rho
     float omega_f, rho0_f, u0x_f, u0y_f, th0_f, b0_f, r0x_f, r0y_f, T0_f, scale_f, inv_scale_f;
     float H0rest_f, H0e_f[NPAIR_MAX], H0o_f[NPAIR_MAX], E2_0_f[NSHELL_MAX], O1_0_f[NSHELL_MAX];
 #ifdef LBM_BOUNDS
@@ -72,8 +82,13 @@ struct alignas(256) RunDev {
 // Classes: the interior tiles; the frame launch (ring blocks, then frame blocks); the phase-A
 // launch (ring blocks, then frame blocks if the run has a PML); the characteristic targets of
 // runs that select the PML moments (ring blocks).
-enum Cls { CLS_BULK = 0, CLS_FRAME = 1, CLS_A = 2, CLS_TGT = 3, NCLS = 4 };
+// Two-step passes add the two-step tiles and the second step's frame launch (ring, frame and shell
+// blocks).
+enum Cls { CLS_BULK = 0, CLS_FRAME = 1, CLS_A = 2, CLS_TGT = 3, CLS_CORE = 4, CLS_FRAME2 = 5, NCLS = 6 };
 struct KernelSet;
+
+// Position of a sub-step in its batch: time steps and population buffer swaps since its start.
+struct Sub { int steps, flips; };
 struct LaunchSet {
     const KernelSet *ks;      // kernels of the runs' velocity stencil (one stencil per set)
     RunDev *const *runs;      // device array of descriptor pointers
@@ -82,7 +97,32 @@ struct LaunchSet {
     int nruns;
     int poison = 0;           // debug canary: NaN-fill each step's destination buffers first
     int split = -1;           // fused grid: phase-A blocks after split/8 of the tiles; -1 default
+    int core_rows = 0;        // rows of a two-step tile; 0: the set takes single steps only
 };
+
+// Two-step tiles: CORE_X columns of the level between, CORE_R rows per turn (one wave each); they
+// advance core_out columns by two steps.  CORE_PAD: LDS elements before and after the rows, which
+// the lanes that advance no node may read.
+constexpr int CORE_X = 64, CORE_R = 4, CORE_PAD = 8, CORE_LINE = 64;
+// Columns a tile advances: whole CORE_LINE-byte pieces of a population row, from a column that starts one.
+constexpr int core_out(int reach, int es) { return (CORE_X - 2 * reach) * es / CORE_LINE * CORE_LINE / es; }
+inline __host__ __device__ int core_x0(int fx0, int reach, int es) { return (fx0 + reach) * es / CORE_LINE * CORE_LINE / es; }
+// LDS rows of a tile: CORE_R per population, and one more for each row pulled two turns later.
+constexpr int core_lds_rows(const LatticeInfo &l) {
+    int n = 0;
+    for (int i = 0; i < l.q; ++i) {
+        const int delay = l.ey(i) + reach_of(l);
+        n += CORE_R + (delay > CORE_R ? delay - CORE_R : 0);
+    }
+    return n;
+}
+// Tiles a compute unit holds (160 KiB of LDS, allotted in 1280 bytes; at most 4 waves per SIMD)
+// and their waves per SIMD, which bound the kernel's registers.
+constexpr int core_tiles_per_cu(const LatticeInfo &l, int es) {
+    const int bytes = ((core_lds_rows(l) * CORE_X + 2 * CORE_PAD) * es + 1279) / 1280 * 1280;
+    return 163840 / bytes < 4 ? 163840 / bytes : 4;
+}
+constexpr int core_waves(const LatticeInfo &l, int es) { return core_tiles_per_cu(l, es) * CORE_R / 4; }
 
 constexpr int FRAME_BLOCK = 256;
 // Ring nodes per block of the boundary launches: one active wave per 256-thread block, so the
@@ -108,19 +148,19 @@ __host__ __device__ inline int frame_block_count(int frame_n) {
 struct KernelSet {
     int q;
     // step kernels of sub-step ks of a batch (parity par + ks; active while step + ks < limit)
-    hipError_t (*phase_a)(const LaunchSet &L, int storage, int ks, hipStream_t s);
+    hipError_t (*phase_a)(const LaunchSet &L, int storage, Sub ks, hipStream_t s);
     // frame, phase_a_bulk and bulk take optional events a and b (both or neither), attached to
     // the dispatch: they take the kernel's own start and end time
-    hipError_t (*frame)(const LaunchSet &L, int storage, int ks, hipStream_t s, hipEvent_t a,
+    hipError_t (*frame)(const LaunchSet &L, int storage, Sub ks, hipStream_t s, hipEvent_t a,
                         hipEvent_t b);
-    hipError_t (*target)(const LaunchSet &L, int storage, int ks, hipStream_t s);
+    hipError_t (*target)(const LaunchSet &L, int storage, Sub ks, hipStream_t s);
     // phase A and the bulk tiles in one launch
-    hipError_t (*phase_a_bulk)(const LaunchSet &L, int storage, int tx, int ks, hipStream_t s,
+    hipError_t (*phase_a_bulk)(const LaunchSet &L, int storage, int tx, Sub ks, hipStream_t s,
                                hipEvent_t a, hipEvent_t b);
-    hipError_t (*bulk)(const LaunchSet &L, int storage, int tx, int ks, hipStream_t s,
+    hipError_t (*bulk)(const LaunchSet &L, int storage, int tx, Sub ks, hipStream_t s,
                        hipEvent_t a, hipEvent_t b);
-    // end of a batch of n sub-steps: step counters and parities advance
-    hipError_t (*advance)(const LaunchSet &L, int n, hipStream_t s);
+    // end of a batch of n sub-steps with `flips` buffer swaps: step counters and parities advance
+    hipError_t (*advance)(const LaunchSet &L, int n, int flips, hipStream_t s);
     hipError_t (*set_limit)(RunDev *run, long long limit, hipStream_t s);
     hipError_t (*set_limits)(RunDev *const *runs, const long long *limits, int n, hipStream_t s);
     hipError_t (*init)(RunDev *run, int storage, int Nx, int Ny, const double *rho,
@@ -142,7 +182,9 @@ struct KernelSet {
                                  double *partials, hipStream_t s);
     hipError_t (*err_final)(const double *partials, int nrows, double *out, hipStream_t s);
     // debug canary of sub-step ks: NaN into the buffers the step writes in full (every active run)
-    hipError_t (*poison)(const LaunchSet &L, int storage, int ks, hipStream_t s);
+    hipError_t (*poison)(const LaunchSet &L, int storage, Sub ks, hipStream_t s);
+    // two time steps from sub-step k1 on, one pass over the interior
+    hipError_t (*two_steps)(const LaunchSet &L, int storage, Sub k1, hipStream_t s);
 };
 
 namespace k37 { extern const KernelSet kernels; }

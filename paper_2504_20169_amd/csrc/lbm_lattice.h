@@ -22,6 +22,13 @@ constexpr int NQ_MAX = 37;
 constexpr int NPAIR_MAX = 18;
 constexpr int NSHELL_MAX = 8;
 
+// Coefficients of the equilibrium as a polynomial in the integer components of e, with v = r u:
+// rho H = E0 + n E1 + n^2 E2 + ex^2 (BXX + n TXX) + ex ey (BXY + n TXY) + ey^2 (BYY + n TYY)
+//       + ex^4 Q40 + ex^3 ey Q31 + ex^2 ey^2 Q22 + ex ey^3 Q13 + ey^4 Q04
+//       + ex (LX + n MX) + ey (LY + n MY) + ex^3 C30 + ex^2 ey C21 + ex ey^2 C12 + ey^3 C03.
+enum EqCoef { E0, E1, E2, BXX, BXY, BYY, TXX, TXY, TYY, Q40, Q31, Q22, Q13, Q04,
+              LX, LY, MX, MY, C30, C21, C12, C03, NEQ };
+
 namespace d2q37 {
 constexpr int NQ = 37;
 constexpr int NPAIR = 18;
@@ -97,17 +104,28 @@ constexpr int ey_of(int i) { return i == 0 ? 0 : ((i - 1) & 1) ? -PEY[(i - 1) >>
 constexpr int shell_of(int i) { return i == 0 ? 0 : PSH[(i - 1) >> 1]; }
 }  // namespace d2q9
 
-// Host view of one stencil's tables.
+// Host view of one stencil's tables (and their reach, for the kernels).
 struct LatticeInfo {
     int q, npair, nshell, order;
     double r;
     const int *shell_e2;
     const double *shell_w;
     const int *pex, *pey, *psh;
-    int ex(int i) const { return i == 0 ? 0 : ((i - 1) & 1) ? -pex[(i - 1) >> 1] : pex[(i - 1) >> 1]; }
-    int ey(int i) const { return i == 0 ? 0 : ((i - 1) & 1) ? -pey[(i - 1) >> 1] : pey[(i - 1) >> 1]; }
+    constexpr int ex(int i) const { return i == 0 ? 0 : ((i - 1) & 1) ? -pex[(i - 1) >> 1] : pex[(i - 1) >> 1]; }
+    constexpr int ey(int i) const { return i == 0 ? 0 : ((i - 1) & 1) ? -pey[(i - 1) >> 1] : pey[(i - 1) >> 1]; }
     int shell(int i) const { return i == 0 ? 0 : psh[(i - 1) >> 1]; }
 };
+
+// Longest displacement of a stencil along an axis, in cells.
+constexpr int reach_of(const LatticeInfo &l) {
+    int m = 0;
+    for (int i = 0; i < l.q; ++i) {
+        const int a = l.ex(i) < 0 ? -l.ex(i) : l.ex(i), b = l.ey(i) < 0 ? -l.ey(i) : l.ey(i);
+        m = a > m ? a : m;
+        m = b > m ? b : m;
+    }
+    return m;
+}
 
 inline constexpr LatticeInfo LATTICE_D2Q37 = {d2q37::NQ, d2q37::NPAIR, d2q37::NSHELL, d2q37::ORDER,
                                               d2q37::LAT_R, d2q37::SHELL_E2, d2q37::SHELL_W,
