@@ -104,6 +104,36 @@ struct DeviceMem {
     }
 };
 
+// Pinned host memory of one run for what a call brings to or from the host, kept up to MOST bytes.  A
+// small pageable copy costs about 20 us whatever its size (four fields of a 220 x 20 grid: 58 us, as
+// one pinned copy 9-13 us); from a megabyte on the two are even.  Every call that uses it drains
+// the run's stream before it returns.
+struct HostStage {
+    static constexpr size_t MOST = 1 << 20;
+    void *p = nullptr;
+    size_t cap = 0;
+    // at least `bytes` of pinned memory, or NULL: the caller then copies to pageable memory
+    char *get(size_t bytes) {
+        if (bytes > MOST) return nullptr;
+        if (bytes > cap) {
+            release();
+            const size_t want = std::max<size_t>((size_t)round_up((long long)bytes, 4096), 4096);
+            if (hipHostMalloc(&p, want, hipHostMallocDefault) != hipSuccess) {
+                (void)hipGetLastError();
+                p = nullptr;
+                return nullptr;
+            }
+            cap = want;
+        }
+        return (char *)p;
+    }
+    void release() {
+        if (p) (void)hipHostFree(p);
+        p = nullptr;
+        cap = 0;
+    }
+};
+
 int tx_index(int tx) { return tx == 64 ? 0 : tx == 128 ? 1 : 2; }
 
 // Side stream and events of the per-step fork/join: the bulk kernel runs on the main stream while
@@ -182,6 +212,7 @@ struct lbm_run {
     lbm_group *group = nullptr;
     size_t footprint = 0;
     int *dflag = nullptr;             // lbm_check's flag, allocated with the run
+    HostStage stage;
     unsigned debug = 0;               // lbm_set_debug flags
     int64_t check_every = 0;          // lbm_set_check_interval: steps between checks in lbm_step
     StepStreams ss;
@@ -1052,9 +1083,16 @@ lbm_status lbm_moments(lbm_handle h, double *rho, double *ux, double *uy, double
     hipError_t e = h->ks->moments(h->dd, h->desc.storage, R.Nx, R.Ny, o[0] ? d[0] : nullptr,
                                   o[1] ? d[1] : nullptr, o[2] ? d[2] : nullptr, o[3] ? d[3] : nullptr,
                                   h->stream);
-    for (int k = 0; k < 4 && e == hipSuccess; ++k)
-        if (o[k]) e = hipMemcpyAsync(o[k], d[k], nn * sizeof(double), hipMemcpyDeviceToHost, h->stream);
+    char *stage = h->stage.get(4 * nn * sizeof(double));
+    if (stage) {
+        if (e == hipSuccess) e = hipMemcpyAsync(stage, tmp, 4 * nn * sizeof(double), hipMemcpyDeviceToHost, h->stream);
+    } else {
+        for (int k = 0; k < 4 && e == hipSuccess; ++k)
+            if (o[k]) e = hipMemcpyAsync(o[k], d[k], nn * sizeof(double), hipMemcpyDeviceToHost, h->stream);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    for (int k = 0; stage && k < 4 && e == hipSuccess; ++k)
+        if (o[k]) std::memcpy(o[k], stage + k * nn * sizeof(double), nn * sizeof(double));
     h->mem.put(tmp);
     if (e != hipSuccess) return fail(LBM_ERR_DEVICE, std::string("lbm_moments: ") + hipGetErrorString(e));
     return LBM_OK;
@@ -1104,14 +1142,24 @@ lbm_status lbm_error_norms(lbm_handle h, const double *ref_rho, const double *re
     double *m = tmp, *refs = tmp + 3 * nn, *part = refs + 3 * nb, *dout = part + 3 * (size_t)ly;
     hipError_t e = h->ks->moments(h->dd, h->desc.storage, R.Nx, R.Ny, m, m + nn, nullptr, m + 2 * nn, h->stream);
     const double *src[3] = {ref_rho, ref_ux, ref_T};
-    for (int k = 0; k < 3 && e == hipSuccess; ++k)
-        e = hipMemcpyAsync(refs + k * nb, src[k], nb * sizeof(double), hipMemcpyHostToDevice, h->stream);
+    // pinned: the references, then the three norms
+    double *stage = (double *)h->stage.get((3 * nb + 3) * sizeof(double));
+    if (stage) {
+        for (int k = 0; k < 3; ++k) std::memcpy(stage + k * nb, src[k], nb * sizeof(double));
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(refs, stage, 3 * nb * sizeof(double), hipMemcpyHostToDevice, h->stream);
+    } else {
+        for (int k = 0; k < 3 && e == hipSuccess; ++k)
+            e = hipMemcpyAsync(refs + k * nb, src[k], nb * sizeof(double), hipMemcpyHostToDevice, h->stream);
+    }
+    double *hout = stage ? stage + 3 * nb : out;
     if (e == hipSuccess)
         e = h->ks->err_rows(m, m + nn, m + 2 * nn, R.Nx, R.Wxm, R.Wym, h->desc.nx, ly, refs, refs + nb,
                             refs + 2 * nb, part, h->stream);
     if (e == hipSuccess) e = h->ks->err_final(part, ly, dout, h->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(out, dout, 3 * sizeof(double), hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(hout, dout, 3 * sizeof(double), hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (stage && e == hipSuccess) std::memcpy(out, hout, 3 * sizeof(double));
     h->mem.put(tmp);
     if (e != hipSuccess) return fail(LBM_ERR_DEVICE, std::string("lbm_error_norms: ") + hipGetErrorString(e));
     return LBM_OK;
@@ -1178,10 +1226,12 @@ lbm_status lbm_check(lbm_handle h) {
     if (!h->inited) return fail(LBM_ERR_STATE, "not initialised");
     int *flag = h->dflag;
     int hf = 0;
+    int *stage = (int *)h->stage.get(sizeof(int)), *hflag = stage ? stage : &hf;
     hipError_t e = hipMemsetAsync(flag, 0, sizeof(int), h->stream);
     if (e == hipSuccess) e = h->ks->check(h->dd, h->desc.storage, h->hd.Nx, h->hd.Ny, flag, h->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&hf, flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e == hipSuccess) hf = *hflag;
     if (e != hipSuccess) return fail(LBM_ERR_DEVICE, std::string("lbm_check: ") + hipGetErrorString(e));
     if (hf & 2) return fail(LBM_ERR_DEVICE, "a kernel met an index out of range (bounds-checked build)");
     if (hf) return fail(LBM_ERR_UNSTABLE, "non-finite value, rho <= 0 or T <= 0 in the state");
@@ -1236,6 +1286,7 @@ void lbm_destroy(lbm_handle h) {
     for (auto &ev : h->pending) { (void)hipEventDestroy(ev.a); (void)hipEventDestroy(ev.b); }
     for (auto e : h->pool) (void)hipEventDestroy(e);
     h->mem.release_all();
+    h->stage.release();
     h->ss.destroy();
     if (h->own_stream) (void)hipStreamDestroy(h->own_stream);
     delete h;
