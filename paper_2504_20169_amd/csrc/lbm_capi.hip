@@ -484,6 +484,9 @@ void compute_blocks(const RunDev &R, int tx, int rows, int reach, int nb[NCLS]) 
     nb[CLS_FRAME] = rb + fb;
     nb[CLS_A] = rb + (R.has_q ? fb : 0);
     nb[CLS_TGT] = R.tgt_pre ? rb : 0;
+    const int fs = ((R.ann_n + SPLIT_BLOCK - 1) / SPLIT_BLOCK + 7) & ~7;
+    nb[CLS_SPLIT] = rb + fs;
+    nb[CLS_A_SPLIT] = rb + (R.has_q ? fs : 0);
     const bool two = rows > 0 && R.core_strips > 0;
     const int hc = R.fy1 - R.fy0 - 2 * reach;
     nb[CLS_CORE] = two ? R.core_strips * ((hc + rows - 1) / rows) : 0;
@@ -536,6 +539,12 @@ lbm_status upload_prefix(lbm_run *h) {
     return LBM_OK;
 }
 
+// Whether a set's boundary leaves the device so idle that its launches split each node's populations
+// over four waves.
+bool split_small(const LaunchSet &L, const lbm_run *h) {
+    return L.blocks[CLS_SPLIT] <= split_most(h->lat->q, (int)elem_size(h->desc.storage));
+}
+
 LaunchSet single_set(lbm_run *h) {
     LaunchSet L;
     L.ks = h->ks;
@@ -546,6 +555,7 @@ LaunchSet single_set(lbm_run *h) {
     }
     L.poison = (h->debug & LBM_DEBUG_POISON) ? 1 : 0;
     L.split = h->launch.split;
+    L.split_small = split_small(L, h);
     L.core_rows = h->launch.overlap == 2 && !h->prof && !L.poison ? h->core_rows : 0;
     L.nruns = 1;
     return L;
@@ -1601,6 +1611,7 @@ lbm_status lbm_group_step(lbm_group_handle g, const int64_t *steps, int64_t nste
     L.nruns = (int)n;
     L.poison = g->poison;
     L.split = g->launch.split;
+    L.split_small = split_small(L, g->members[0]);
     L.core_rows = g->launch.overlap == 2 && !g->poison ? g->core_rows : 0;
     // Runs past their own count skip every kernel, so whole graphs of G batched steps serve any
     // mix of counts; the remainder is launched eagerly.

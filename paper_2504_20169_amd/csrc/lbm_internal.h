@@ -83,8 +83,8 @@ struct alignas(256) RunDev {
 // launch (ring blocks, then frame blocks if the run has a PML); the characteristic targets of
 // runs that select the PML moments (ring blocks).
 // Two-step passes add the two-step tiles and the second step's frame launch (ring, frame and shell
-// blocks).
-enum Cls { CLS_BULK = 0, CLS_FRAME = 1, CLS_A = 2, CLS_TGT = 3, CLS_CORE = 4, CLS_FRAME2 = 5, NCLS = 6 };
+// blocks); a small frame is launched in blocks that split the populations (ring, then frame), phase A likewise.
+enum Cls { CLS_BULK = 0, CLS_FRAME = 1, CLS_A = 2, CLS_TGT = 3, CLS_CORE = 4, CLS_FRAME2 = 5, CLS_SPLIT = 6, CLS_A_SPLIT = 7, NCLS = 8 };
 struct KernelSet;
 
 // Position of a sub-step in its batch: time steps and population buffer swaps since its start.
@@ -98,6 +98,7 @@ struct LaunchSet {
     int poison = 0;           // debug canary: NaN-fill each step's destination buffers first
     int split = -1;           // fused grid: phase-A blocks after split/8 of the tiles; -1 default
     int core_rows = 0;        // rows of a two-step tile; 0: the set takes single steps only
+    bool split_small = false; // boundary launches of single steps split a node's populations over 4 waves
 };
 
 // Two-step tiles: CORE_X columns of the level between, CORE_R rows per turn (one wave each); they
@@ -129,6 +130,17 @@ constexpr int FRAME_BLOCK = 256;
 // ring's few, poorly coalesced waves (a 3-wide strip puts ~21 grid rows in one wave) land on
 // different compute units instead of sharing one unit's memory pipeline four at a time.
 constexpr int RING_BLOCK = 64;
+// Nodes per block of the boundary kernels that split their populations over its 4 waves, and the most
+// such blocks of a launch set for which they are taken (256 CUs times those a CU holds at once; a
+// second round of blocks costs more than the split gains).  Frame launch and fused launch together,
+// us, split and not, below and above the line: D2Q37 FP64 340^2 33.7, 37.0, 490^2 (720 blocks) 53.6,
+// 52.4; FP32 490^2 33.5, 37.5, 740^2 (1100) 54.6, 52.1; D2Q17 FP64 490^2 28.0, 29.3, 560^2 (810)
+// 33.1, 32.7; FP32 640^2 24.5, 26.4, 880^2 (1260) 36.7, 37.9.
+constexpr int SPLIT_BLOCK = 64;
+constexpr int split_most(int q, int elem) {
+    return 256 * (q == 37 ? (elem == 8 ? 2 : 4) : q == 17 ? (elem == 8 ? 3 : 5) : 0);
+}
+static_assert(SPLIT_BLOCK == RING_BLOCK, "the split launch has the ring's blocks");
 
 // Blocks of a run in the boundary launches: ring blocks, then frame blocks, each count rounded up
 // to a multiple of 8.  Blocks are dealt round-robin to the 8 XCDs, so every run's frame blocks

@@ -759,30 +759,35 @@ __device__ __forceinline__ void for_each_poly(CRun &R, const Mom<C> &m, const K<
     });
 }
 
-// Collision of a node from its populations g (deviations): BGK, g + omega (feq - g), and with PML
-// the term -2 sigma fhat (s = sigma; with sigma = 0 it leaves BGK's bits); emit(i, out) gets each
-// population as it is done.  (feq - g is formed whole: it is small near equilibrium, so the
+// Collision of population i (deviation g): BGK, g + omega (feq - g), and with PML the term
+// -2 sigma fhat (s = sigma; with sigma = 0 it leaves BGK's bits).  t: (feq - fbar) / w in FP64
+// storage, else feq - fbar.  (feq - g is formed whole: it is small near equilibrium, so the
 // relaxation rounds once at the populations' scale.)
-template <bool PML, class S, class C, class F>
-__device__ __forceinline__ void collide(CRun &R, const K<C> &k, const Mom<C> &m, const C (&g)[NQ], C s, F &&emit) {
+template <bool PML, int i, class S, class C>
+__device__ __forceinline__ C relax(C g, C t, C omega, C s) {
     if constexpr (std::is_same<S, double>::value) {
-        for_each_poly<C>(R, m, k, [&](auto ic, C t) {
-            constexpr int i = decltype(ic)::value;
-            C out = g[i] + k.omega * (C(weight_of<i>()) * t - g[i]);
-            if constexpr (PML) out -= s * (C(2 * weight_of<i>()) * t);
-            emit(ic, out);
-        });
+        C out = g + omega * (C(weight_of<i>()) * t - g);
+        if constexpr (PML) out -= s * (C(2 * weight_of<i>()) * t);
+        return out;
     } else {
-        const Eq<C> q = eq_coef<C>(m.drho, m.dux, m.duy, m.dT, k);
-        for_each_feq<C>(q, R, k, [&](auto ic, C fe) {
-            constexpr int i = decltype(ic)::value;
-            C out = g[i] + k.omega * (fe - g[i]);
-            if constexpr (PML) out = out - s * (C(2) * fe);
-            emit(ic, out);
-        });
+        C out = g + omega * (t - g);
+        if constexpr (PML) out = out - s * (C(2) * t);
+        return out;
     }
 }
 
+// Collision of a node from its populations; emit(i, out) gets each population as it is done.
+template <bool PML, class S, class C, class F>
+__device__ __forceinline__ void collide(CRun &R, const K<C> &k, const Mom<C> &m, const C (&g)[NQ], C s, F &&emit) {
+    auto one = [&](auto ic, C t) {
+        constexpr int i = decltype(ic)::value;
+        emit(ic, relax<PML, i, S, C>(g[i], t, k.omega, s));
+    };
+    if constexpr (std::is_same<S, double>::value)
+        for_each_poly<C>(R, m, k, one);
+    else
+        for_each_feq<C>(eq_coef<C>(m.drho, m.dux, m.duy, m.dT, k), R, k, one);
+}
 // ------------------------------------------------------------------------------------------
 // characteristic boundary (float64 always)
 // ------------------------------------------------------------------------------------------
@@ -1163,6 +1168,16 @@ __device__ __forceinline__ QStencil<C> q_stencil(CRun &R, int x, int y, int t) {
     return q;
 }
 
+// The rest of the PML term of population i, -sigma (e.grad Q + sigma Q), added to h; v: Q at the node,
+// its x neighbours and its y neighbours.
+template <int i, class C>
+__device__ __forceinline__ C pml_gradient(const QStencil<C> &q, const C (&v)[5], C h, C s) {
+    C gq = C(0);
+    if constexpr (ex_of(i) != 0) gq += C(ex_of(i)) * (q.cxs * v[0] + q.cx0 * v[1] + q.cx1 * v[2]);
+    if constexpr (ey_of(i) != 0) gq += C(ey_of(i)) * (q.cys * v[0] + q.cy0 * v[3] + q.cy1 * v[4]);
+    return h - s * (gq + s * v[0]);
+}
+
 // Appendix (eq. NSF-CHAR-PML): with a PML the macroscopic equations carry source terms built
 // from the auxiliary moments; with phi = (1, xi_x, xi_y, |xi|^2/2) the selected parts
 // I = sum phi_i e_i . grad Q_i (bit 0), II = 2 sum phi_i fhat_i (bit 1) and
@@ -1281,21 +1296,25 @@ __global__ __launch_bounds__(256) void k_target(RunDev *const *__restrict__ runs
 // their targets ahead, the target of k_target; then the clamped pull of x_f and the
 // non-equilibrium extrapolation into G (ring index tt), where the Q update, the frame kernel and
 // the moment export read it.
-template <int SRC, class S, class C>
-__device__ __forceinline__ void nrbc_node(CRun &R, int par, int up, int tt, int x, int y, int t, C inv_scale) {
-    const GLOBAL double *Uc = (const GLOBAL double *)R.U[up];
+__device__ __forceinline__ void ring_target(CRun &R, const GLOBAL double *Uc, int x, int y, int t, double (&Ut)[4]) {
     const unsigned qp = (unsigned)R.qplane;
     const bool pre = R.tgt_pre != 0;
     const GLOBAL double *Ub = pre ? (const GLOBAL double *)R.P : Uc;
-    const unsigned ib = pre ? (unsigned)tt : (unsigned)t, sb = pre ? (unsigned)R.rplane : qp;
-    double Ut[4] = {Ub[ib], Ub[sb + ib], Ub[2 * sb + ib], Ub[3 * sb + ib]};
+    const unsigned sb = pre ? (unsigned)R.rplane : qp;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) Ut[c] = Ub[c * sb + (unsigned)t];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         bool on = s == XMIN ? x < 3 : s == XMAX ? x >= R.Nx - 3 : s == YMIN ? y < 3 : y >= R.Ny - 3;
         // (runs with a CBC (A) side always form their targets ahead: pre is set)
         if (on && !pre && R.bc[s] == BC_NRBC) lodi_add(R, Uc, s, x, y, t, Ut);
     }
-    nrbc_fill<SRC, S, C>(R, pull_base<SRC, S>(R, par), x, y, inv_scale, Ut, tt);
+}
+template <int SRC, class S, class C>
+__device__ __forceinline__ void nrbc_node(CRun &R, int par, int up, int x, int y, int t, C inv_scale) {
+    double Ut[4];
+    ring_target(R, (const GLOBAL double *)R.U[up], x, y, t, Ut);
+    nrbc_fill<SRC, S, C>(R, pull_base<SRC, S>(R, par), x, y, inv_scale, Ut, t);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1388,7 +1407,6 @@ __device__ __forceinline__ void frame_collide(CRun &R, const K<C> &k, const C (&
     if (R.has_q) {
         const QStencil<C> qs = q_stencil<C>(R, x, y, t);
         const unsigned ot = qs.ot, ox0 = qs.ox0, ox1 = qs.ox1, oy0 = qs.oy0, oy1 = qs.oy1;
-        const C cxs = qs.cxs, cx0 = qs.cx0, cx1 = qs.cx1, cys = qs.cys, cy0 = qs.cy0, cy1 = qs.cy1;
         // sigma = 0 off the layer: the PML terms are then -0 * (finite) and leave BGK's bits
         const C s = (C)(R.W > 0 ? sigma_at(R, x, y) : 0.0);
         C h[NQ];
@@ -1407,13 +1425,7 @@ __device__ __forceinline__ void frame_collide(CRun &R, const K<C> &k, const C (&
             });
             static_for<c0, c1>([&](auto ic) {
                 constexpr int i = decltype(ic)::value, l = i - c0;
-                C gq = C(0);
-                if constexpr (ex_of(i) != 0)
-                    gq += C(ex_of(i)) * (cxs * v[l][0] + cx0 * v[l][1] + cx1 * v[l][2]);
-                if constexpr (ey_of(i) != 0)
-                    gq += C(ey_of(i)) * (cys * v[l][0] + cy0 * v[l][3] + cy1 * v[l][4]);
-                C out = h[i] - s * (gq + s * v[l][0]);
-                put(ic, out);
+                put(ic, pml_gradient<i>(qs, v[l], h[i], s));
             });
         });
     } else {
@@ -1423,6 +1435,13 @@ __device__ __forceinline__ void frame_collide(CRun &R, const K<C> &k, const C (&
     Un[qp + t] = R.u0x + (double)m.dux;
     Un[2 * qp + t] = R.u0y + (double)m.duy;
     Un[3 * qp + t] = R.T0 + (double)m.dT;
+}
+
+// Barrier that orders LDS accesses only: loads from memory stay in flight across it.
+__device__ __forceinline__ void core_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Second step of a two-step pass on shell node ts (strip numbering of the REACH interior layers
@@ -1511,13 +1530,6 @@ __device__ __forceinline__ void row_store(const Rows<S> &a, unsigned off, S v) {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), a.r, off, so, 2);
     else
         __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), a.r, off, so, 2);
-}
-
-// Barrier that orders LDS accesses only: loads from memory stay in flight across it.
-__device__ __forceinline__ void core_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 template <class S>
@@ -1716,6 +1728,158 @@ __global__ __launch_bounds__(256) void k_frame(RunDev *const *__restrict__ runs,
     }
 }
 
+#if LBM_Q >= 17   // D2Q9 has fewer duos than waves
+// Kernels whose 4 waves share 64 nodes: wave W of a block has the duos [D0, D1) of each node's
+// populations (and wave 0 the rest population), kept in registers in the order of index(), the rest
+// population first.  What a wave needs of all populations (the moments) it sums from LDS, where
+// the waves lay their own.  Only the steps on a wave's own populations are compiled per wave
+// (by_wave); all else is one code, so that the four waves fetch the same instructions.
+template <int W> struct Share {
+    static constexpr int D0 = NDUO * W / 4, D1 = NDUO * (W + 1) / 4;
+    static constexpr bool REST = W == 0;
+    static constexpr int N = 4 * (D1 - D0) + REST;
+    static constexpr int index(int l) { return REST && l == 0 ? 0 : 1 + 4 * D0 + l - REST; }
+    static constexpr int local(int i) { return i == 0 ? 0 : i - 1 - 4 * D0 + REST; }
+};
+constexpr int SHARE = 4 * ((NDUO + 3) / 4) > Share<0>::N ? 4 * ((NDUO + 3) / 4) : Share<0>::N;   // the most of a wave
+
+template <class F> __device__ __forceinline__ void by_wave(int w, F &&f) {
+    if (w == 0) f(Share<0>{});
+    else if (w == 1) f(Share<1>{});
+    else if (w == 2) f(Share<2>{});
+    else f(Share<3>{});
+}
+template <class H, class C> __device__ __forceinline__ void share_put(C *lds, int lane, const C (&v)[SHARE]) {
+    static_for<0, H::N>([&](auto lc) { lds[H::index(decltype(lc)::value) * SPLIT_BLOCK + lane] = v[decltype(lc)::value]; });
+}
+// A wave's populations of the equilibrium of one state, or of two: emit(i, t, ...), t as in relax().
+template <class H, class C, class F>
+__device__ __forceinline__ void share_eq(CRun &R, const K<C> &, const EqPoly<C> &q, F &&emit) {
+    if constexpr (H::REST) emit(std::integral_constant<int, 0>{}, q.c[E0]);
+    poly_duos<H::D0, H::D1>(q, emit);
+}
+template <class H, class C, class F>
+__device__ __forceinline__ void share_eq(CRun &R, const K<C> &k, Eq<C> q, F &&emit) {
+    if constexpr (H::REST) emit(std::integral_constant<int, 0>{}, feq_rest<C>(q, R));
+    static_for<2 * H::D0, 2 * H::D1>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        if constexpr (p == 2 * H::D0 || PSH[p - 1] != PSH[p]) eq_shell<C, PSH[p]>(q);
+        C fp, fm;
+        eq_pair<C, p>(q, R, k, fp, fm);
+        emit(std::integral_constant<int, 1 + 2 * p>{}, fp);
+        emit(std::integral_constant<int, 2 + 2 * p>{}, fm);
+    });
+}
+template <class H, class C, class F>
+__device__ __forceinline__ void share_eq2(CRun &R, const K<C> &k, Eq<C> qa, Eq<C> qb, F &&emit) {
+    if constexpr (H::REST) emit(std::integral_constant<int, 0>{}, feq_rest<C>(qa, R), feq_rest<C>(qb, R));
+    if constexpr (H::D0 > 0 && PSH[2 * H::D0 - 1] == PSH[2 * H::D0]) {   // (feq2_pairs sets a shell at its first pair)
+        eq_shell<C, PSH[2 * H::D0]>(qa);
+        eq_shell<C, PSH[2 * H::D0]>(qb);
+    }
+    feq2_pairs<2 * H::D0, 2 * H::D1>(qa, qb, R, k, emit);
+}
+
+// The single step on the frame where its nodes leave the device idle: the waves of a block share the
+// nodes, each pulling and colliding its populations with every Q it needs in flight at once; the
+// sums are those of moments() in order, so the bits are those of k_frame.  There a lone wave
+// issues at half rate and waits most of its time, so a node's chain of loads and arithmetic is what
+// the launch takes.  By k_frame and here, us, D2Q37: FP64 120^2 13.2, 8.1; 190^2 13.4, 9.5; 340^2
+// 15.0, 13.3; FP32 140^2 10.2, 7.7; 490^2 13.4, 12.4; FP16 140^2 9.9, 7.7; 490^2 12.2, 11.4.  D2Q17:
+// FP64 340^2 9.3, 8.0; 490^2 10.7, 10.3; FP32 340^2 8.2, 7.1; 880^2 10.5, 10.3; FP16 490^2 8.2, 7.7.
+template <class S>
+__global__ __launch_bounds__(256) void k_frame_split(RunDev *const *__restrict__ runs,
+                                                     const int *__restrict__ prefix, int nruns, Sub ks) {
+    using C = typename Traits<S>::C;
+    __shared__ C lds[NQ * SPLIT_BLOCK];
+    const int b = blockIdx.x;
+    const int j = find_run(prefix, nruns, b);
+    CRun &R = run_of(runs, j);
+    const int par = sub_par(R, ks);
+    if (par < 0) return;
+    const int tb = b - ((const CONSTANT int *)prefix)[j];
+    const int rb = ring_blocks(R);
+    const bool ring = tb < rb;
+    const int lane = (int)threadIdx.x & (SPLIT_BLOCK - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / SPLIT_BLOCK);
+    const int n = (ring ? tb : tb - rb) * SPLIT_BLOCK + lane, count = ring ? R.ring_n : R.ann_n;
+    if (n - lane >= count) return;
+    const int nn = min(n, count - 1);          // every wave of the block meets its barriers
+    int x, y, t;
+    if (ring) {
+        ring_xy(R, nn, x, y);
+        t = (int)LBM_GUARD(R, nn, R.rplane);
+    } else {
+        ann_xy(R, nn, x, y);
+        t = (int)LBM_GUARD(R, R.ann0 + nn, R.qplane);
+    }
+    const K<C> k = load_k<C>(R);
+    const GLOBAL S *src = (const GLOBAL S *)R.f[par];
+    const Pull from = pull_from<SRC_F>(R, x, y);
+    const GLOBAL C *__restrict__ Q = (const GLOBAL C *)R.Q, *__restrict__ G = (const GLOBAL C *)R.G;
+    GLOBAL S *__restrict__ dnode = (GLOBAL S *)R.f[par ^ 1] + (long long)y * R.pitch + x;
+    const unsigned qp = (unsigned)R.qplane, rp = (unsigned)R.rplane;
+    QStencil<C> qs{};
+    C s = C(0);
+    if (R.has_q) {
+        qs = q_stencil<C>(R, x, y, t);
+        s = (C)(R.W > 0 ? sigma_at(R, x, y) : 0.0);
+    }
+    C g[SHARE], v[SHARE][5];
+    by_wave(w, [&](auto h) {
+        using H = decltype(h);
+        if (ring)
+            static_for<0, H::N>([&](auto lc) { g[decltype(lc)::value] = G[H::index(decltype(lc)::value) * rp + t]; });
+        else
+            static_for<0, H::N>([&](auto lc) {
+                constexpr int l = decltype(lc)::value;
+                g[l] = pull_one<SRC_F, S, C, H::index(l)>(R, src, from, k.inv_scale);
+            });
+        if (R.has_q)
+            static_for<0, H::N>([&](auto lc) {
+                constexpr int l = decltype(lc)::value, i = H::index(l);
+                const GLOBAL C *Qi = Q + (long long)i * qp;
+                v[l][0] = *at(Qi, qs.ot);
+                if constexpr (ex_of(i) != 0) { v[l][1] = *at(Qi, qs.ox0); v[l][2] = *at(Qi, qs.ox1); }
+                if constexpr (ey_of(i) != 0) { v[l][3] = *at(Qi, qs.oy0); v[l][4] = *at(Qi, qs.oy1); }
+            });
+        share_put<H>(lds, lane, g);
+    });
+    core_barrier();
+    const Mom<C> m = moments_streamed<NPAIR, C>(
+        [&](auto ic) { return lds[decltype(ic)::value * SPLIT_BLOCK + lane]; }, k);
+    if (n >= count) return;
+    const auto eq = [&] {
+        if constexpr (std::is_same<S, double>::value) return poly_coef<C>(R, m, k);
+        else return eq_coef<C>(m.drho, m.dux, m.duy, m.dT, k);
+    }();
+    by_wave(w, [&](auto h) {
+        using H = decltype(h);
+        auto put = [&](auto ic, C out) {
+            const S o = cvt_out(out, k.scale, (S *)nullptr);
+            dnode[(long long)decltype(ic)::value * R.plane] = o;
+        };
+        if (R.has_q)
+            share_eq<H>(R, k, eq, [&](auto ic, C f) {
+                constexpr int i = decltype(ic)::value, l = H::local(i);
+                put(ic, pml_gradient<i>(qs, v[l], relax<true, i, S, C>(g[l], f, k.omega, s), s));
+            });
+        else
+            share_eq<H>(R, k, eq, [&](auto ic, C f) {
+                constexpr int i = decltype(ic)::value;
+                put(ic, relax<false, i, S, C>(g[H::local(i)], f, k.omega, C(0)));
+            });
+        if constexpr (H::REST) {
+            GLOBAL double *Un = (GLOBAL double *)R.U[u_par(R, ks) ^ 1];
+            Un[t] = R.rho0 + (double)m.drho;
+            Un[qp + t] = R.u0x + (double)m.dux;
+            Un[2 * qp + t] = R.u0y + (double)m.duy;
+            Un[3 * qp + t] = R.T0 + (double)m.dT;
+        }
+    });
+}
+#endif
+
 // PML auxiliary update Q += (fhat^n + fhat^{n+1}) / 2 at frame node t (eq. PMLQ, trapezoid rule),
 // fhat^n from the moment strip of the last level, fhat^{n+1} from m, the moments of g^{n+1}.  Q is
 // read a few pairs at a time (each group's reads issued together, the groups kept apart), so the
@@ -1795,7 +1959,7 @@ __device__ __forceinline__ void phase_a_block(RunDev *const *__restrict__ runs,
         if (tt >= R.ring_n) return;
         ring_xy(R, tt, x, y);
         t = (int)LBM_GUARD(R, tt, R.rplane);
-        nrbc_node<SRC, S, C>(R, par, up, t, x, y, t, k.inv_scale);
+        nrbc_node<SRC, S, C>(R, par, up, x, y, t, k.inv_scale);
         if (!R.has_q || !in_q(R, x, y)) return;
         // the moments of the filled populations, read back from G (this thread's own stores);
         // the opaque index makes the reads form their addresses afresh rather than keep those
@@ -1819,6 +1983,134 @@ __device__ __forceinline__ void phase_a_block(RunDev *const *__restrict__ runs,
     q_update<C>(R, up, k, m, t);
 }
 
+#if LBM_Q >= 17
+// Phase A of block b where its nodes leave the device idle: as k_frame_split, the 4 waves of a block
+// share 64 nodes, each pulling, filling and updating its populations, and what every wave needs
+// of all of them (the moments of the pull, then of the fill) is summed from LDS in the order of
+// moments(), so the bits are those of phase_a_block.  There a lone wave's groups of loads (the pull
+// twice, the fill read back, Q) take some 25 trips to memory one after the other, here four.  What
+// bounds it now is the FP64 arithmetic of the moments and of the two equilibria, which every wave
+// forms.  The fused launch by phase_a_block and here, us, D2Q37: FP64 120^2 12.8, 10.6; 190^2 13.8,
+// 12.5; 340^2 22.0, 20.4; FP32 140^2 14.7, 11.6; 490^2 24.1, 21.1; FP16 140^2 16.7, 11.9; 490^2
+// 21.7, 16.0.  D2Q17: FP64 340^2 12.7, 11.5; 490^2 18.6, 17.8; FP32 340^2 10.0, 9.5; 640^2 16.7,
+// 15.2; FP16 490^2 12.2, 11.5.
+template <class S, int SRC>
+__device__ __forceinline__ void phase_a_split(RunDev *const *__restrict__ runs, const int *__restrict__ prefix,
+                                              int nruns, Sub ks, int b, typename Traits<S>::C *lds) {
+    using C = typename Traits<S>::C;
+    constexpr bool POLY = std::is_same<S, double>::value;
+    const int j = find_run(prefix, nruns, b);
+    CRun &R = run_of(runs, j);
+    const int par = sub_par(R, ks);
+    if (par < 0) return;
+    const int up = u_par(R, ks);
+    const int tb = b - ((const CONSTANT int *)prefix)[j];
+    const int rb = ring_blocks(R);
+    const bool ring = tb < rb;
+    const int lane = (int)threadIdx.x & (SPLIT_BLOCK - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / SPLIT_BLOCK);
+    const int n = (ring ? tb : tb - rb) * SPLIT_BLOCK + lane, count = ring ? R.ring_n : R.ann_n;
+    if (n - lane >= count || (!ring && !R.has_q)) return;
+    const int nn = min(n, count - 1);
+    int x, y, t;
+    if (ring) {
+        ring_xy(R, nn, x, y);
+        t = (int)LBM_GUARD(R, nn, R.rplane);
+    } else {
+        ann_xy(R, nn, x, y);
+        t = (int)LBM_GUARD(R, R.ann0 + nn, R.qplane);
+    }
+    const bool on = n < count, upd = on && R.has_q && in_q(R, x, y);
+    if (!ring && __builtin_amdgcn_ballot_w64(upd) == 0) return;   // the same nodes in every wave
+    const K<C> k = load_k<C>(R);
+    const GLOBAL S *src = pull_base<SRC, S>(R, par);
+    const Pull from = pull_from<SRC>(R, x, y);
+    GLOBAL C *Q = (GLOBAL C *)R.Q;
+    GLOBAL C *G = (GLOBAL C *)R.G;
+    const GLOBAL double *Uc = (const GLOBAL double *)R.U[up];
+    const unsigned qp = (unsigned)R.qplane, rp = (unsigned)R.rplane;
+    const unsigned ot = (unsigned)t * (unsigned)sizeof(C);
+    C g[SHARE], q[SHARE];
+    double u[4] = {};
+    by_wave(w, [&](auto h) {
+        using H = decltype(h);
+        static_for<0, H::N>([&](auto lc) {
+            constexpr int l = decltype(lc)::value;
+            g[l] = pull_one<SRC, S, C, H::index(l)>(R, src, from, k.inv_scale);
+        });
+        if (R.has_q)
+            static_for<0, H::N>([&](auto lc) {
+                q[decltype(lc)::value] = *at(Q + (long long)H::index(decltype(lc)::value) * qp, ot);
+            });
+        share_put<H>(lds, lane, g);
+    });
+    if (R.has_q)
+        for (int c = 0; c < 4; ++c) u[c] = Uc[c * qp + t];
+    auto pulled = [&](auto ic) { return lds[decltype(ic)::value * SPLIT_BLOCK + lane]; };
+    if (ring) {
+        double Ut[4];
+        ring_target(R, Uc, x, y, t, Ut);
+        core_barrier();
+        const K<double> kd = load_k<double>(R);
+        const Mom<double> mf = moments_streamed<6, double>([&](auto ic) { return (double)pulled(ic); }, kd);
+        const Mom<double> mt{Ut[0] - R.rho0, Ut[1] - R.u0x, Ut[2] - R.u0y, Ut[3] - R.T0, 0.0};
+        if constexpr (POLY) {
+            EqPoly<double> e = poly_coef<double>(R, mt, kd);
+            poly_add<-1, double>(e, R, mf, kd);
+            core_barrier();   // every wave has read the pull
+            by_wave(w, [&](auto h) {
+                using H = decltype(h);
+                share_eq<H>(R, kd, e, [&](auto ic, double f) {
+                    constexpr int i = decltype(ic)::value, l = H::local(i);
+                    g[l] = (C)((double)g[l] + weight_of<i>() * f);
+                    if (on) G[i * rp + t] = g[l];
+                });
+                share_put<H>(lds, lane, g);
+            });
+        } else {
+            const Eq<double> ef = eq_coef<double>(mf.drho, mf.dux, mf.duy, mf.dT, kd);
+            const Eq<double> et = eq_coef<double>(mt.drho, mt.dux, mt.duy, mt.dT, kd);
+            core_barrier();
+            by_wave(w, [&](auto h) {
+                using H = decltype(h);
+                share_eq2<H>(R, kd, et, ef, [&](auto ic, double ft, double ff) {
+                    constexpr int i = decltype(ic)::value, l = H::local(i);
+                    g[l] = (C)((double)g[l] + (ft - ff));
+                    if (on) G[i * rp + t] = g[l];
+                });
+                share_put<H>(lds, lane, g);
+            });
+        }
+        if (!R.has_q) return;
+    }
+    core_barrier();
+    const Mom<C> m = moments_streamed<6, C>(pulled, k);
+    if (!upd) return;
+    const Mom<C> m0{(C)(u[0] - R.rho0), (C)(u[1] - R.u0x), (C)(u[2] - R.u0y), (C)(u[3] - R.T0), C(0)};
+    if constexpr (POLY) {
+        EqPoly<C> e = poly_coef<C>(R, m0, k);
+        poly_add<1, C>(e, R, m, k);
+        by_wave(w, [&](auto h) {
+            using H = decltype(h);
+            share_eq<H>(R, k, e, [&](auto ic, C f) {
+                constexpr int i = decltype(ic)::value;
+                *at(Q + (long long)i * qp, ot) = q[H::local(i)] + C(0.5 * weight_of<i>()) * f;
+            });
+        });
+    } else {
+        const Eq<C> q1 = eq_coef<C>(m.drho, m.dux, m.duy, m.dT, k);
+        const Eq<C> q0 = eq_coef<C>(m0.drho, m0.dux, m0.duy, m0.dT, k);
+        by_wave(w, [&](auto h) {
+            using H = decltype(h);
+            share_eq2<H>(R, k, q1, q0, [&](auto ic, C fe1, C fe0) {
+                constexpr int i = decltype(ic)::value;
+                *at(Q + (long long)i * qp, ot) = q[H::local(i)] + C(0.5) * (fe0 + fe1);
+            });
+        });
+    }
+}
+#endif
+
 // Phase A of a step (eq. PMLQ on the Q region; the characteristic fill of the ring).
 template <class S, int SRC>
 __global__ __launch_bounds__(256) void k_phase_a(RunDev *const *__restrict__ runs,
@@ -1832,13 +2124,21 @@ __global__ __launch_bounds__(256) void k_phase_a(RunDev *const *__restrict__ run
 // frame kernel then reads.  nA and h are multiples of 8, so every block keeps its XCD map.  Both
 // paths share one register budget, held at 4 waves per SIMD (128 VGPRs) by the low-register
 // boundary code, the branch-light block dispatch and the occupancy target.
-template <class S, int TX>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_phase_a_bulk(RunDev *const *__restrict__ runs,
+// SPLIT: the phase-A blocks are those of phase_a_split, whose waves run alone or in twos on a SIMD and
+// take up to 256 VGPRs (at 128 they spill: 340^2 D2Q37 FP64 29.2 us against 20.4).
+template <class S, int TX, bool SPLIT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT ? 2 : 4))) void k_phase_a_bulk(RunDev *const *__restrict__ runs,
                                                       const int *__restrict__ preA, int nA,
                                                       const int *__restrict__ preB, int nB, int h,
                                                       int nruns, Sub ks) {
     const int b = blockIdx.x;
     const int pa = b - h;   // blocks [h, h + nA) are phase A; the tiles before and after them
+#if LBM_Q >= 17
+    if constexpr (SPLIT) {
+        __shared__ typename Traits<S>::C lds[NQ * SPLIT_BLOCK];
+        if ((unsigned)pa < (unsigned)nA) return phase_a_split<S, SRC_F>(runs, preA, nruns, ks, pa, lds);
+    }
+#endif
     if ((unsigned)pa < (unsigned)nA) phase_a_block<S, SRC_F>(runs, preA, nruns, ks, pa);
     else bulk_tile<S, TX>(runs, preB, nruns, ks, xcd_swizzle(pa < 0 ? b : b - nA, nB));
 }
@@ -2135,6 +2435,16 @@ static hipError_t launch_target(const LaunchSet &L, int storage, Sub ks, hipStre
 
 static hipError_t launch_frame(const LaunchSet &L, int storage, Sub ks, hipStream_t s, hipEvent_t a,
                                hipEvent_t b) {
+#if LBM_Q >= 17
+    if (const int nb4 = L.blocks[CLS_SPLIT]; nb4 > 0 && L.split_small) {
+        const int *pre = L.prefix[CLS_SPLIT];
+        LBM_DISPATCH(storage, if (a) hipExtLaunchKernelGGL((k_frame_split<S>), dim3(nb4), dim3(256), 0, s, a, b, 0,
+                                                           L.runs, pre, L.nruns, ks);
+                              else hipLaunchKernelGGL((k_frame_split<S>), dim3(nb4), dim3(256), 0, s, L.runs, pre,
+                                                      L.nruns, ks));
+        return hipGetLastError();
+    }
+#endif
     const int nb = L.blocks[CLS_FRAME];
     if (nb <= 0) return hipSuccess;
     const int *pre = L.prefix[CLS_FRAME];
@@ -2167,7 +2477,8 @@ static hipError_t launch_bulk(const LaunchSet &L, int storage, int tx, Sub ks, h
 
 static hipError_t launch_phase_a_bulk(const LaunchSet &L, int storage, int tx, Sub ks, hipStream_t s,
                                       hipEvent_t a, hipEvent_t b) {
-    const int nA = L.blocks[CLS_A], nB = L.blocks[CLS_BULK];
+    const bool split = NQ >= 17 && L.split_small;
+    const int nA = L.blocks[split ? CLS_A_SPLIT : CLS_A], nB = L.blocks[CLS_BULK];
     if (nA + nB <= 0) return hipSuccess;
     // Bulk tiles ahead of the phase-A blocks (by default).  On large grids, where the tiles
     // outnumber the phase-A blocks eightfold or more, all of them: phase A's latency then hides
@@ -2176,21 +2487,27 @@ static hipError_t launch_phase_a_bulk(const LaunchSet &L, int storage, int tx, S
     // against 523.3).  Otherwise half of them for D2Q37 in FP64, where the half after phase A
     // still outlasts its latency (1088^2 NRBC + PML: 178.5 against 185.5 us per step), and none
     // for the rest, where the shorter tiles would leave phase A on the tail (FP32 98.8 against
-    // 97.1 us, FP16 66.6 against 62.0, D2Q9 FP64 47.1 against 46.5).
+    // 97.1 us, FP16 66.6 against 62.0, D2Q9 FP64 47.1 against 46.5).  With split phase-A blocks all
+    // of them in FP64 (D2Q37 at 190^2: 12.5 us, with half 13.9; D2Q17 at 340^2: 11.5, with none 13.2).
     const int h = L.split >= 0 ? (nB * L.split / 8) & ~7
-                  : nB >= 8 * nA ? nB & ~7
+                  : nB >= 8 * nA || (split && storage == ST_F64) ? nB & ~7
                   : (NQ == 37 && storage == ST_F64) ? (nB / 2) & ~7 : 0;
-    const int *pa = L.prefix[CLS_A], *pb = L.prefix[CLS_BULK];
-#define LBM_PAB(TXV)                                                                               \
-    LBM_DISPATCH(storage, if (a) hipExtLaunchKernelGGL((k_phase_a_bulk<S, TXV>), dim3(nA + nB), dim3(256), \
+    const int *pa = L.prefix[split ? CLS_A_SPLIT : CLS_A], *pb = L.prefix[CLS_BULK];
+#define LBM_PAB(TXV, SP)                                                                               \
+    LBM_DISPATCH(storage, if (a) hipExtLaunchKernelGGL((k_phase_a_bulk<S, TXV, SP>), dim3(nA + nB), dim3(256), \
                                                        0, s, a, b, 0, L.runs, pa, nA, pb, nB, h,   \
                                                        L.nruns, ks);                               \
-                          else hipLaunchKernelGGL((k_phase_a_bulk<S, TXV>), dim3(nA + nB), dim3(256), \
+                          else hipLaunchKernelGGL((k_phase_a_bulk<S, TXV, SP>), dim3(nA + nB), dim3(256), \
                                                   0, s, L.runs, pa, nA, pb, nB, h, L.nruns, ks))
-    switch (tx) {
-    case 64: LBM_PAB(64); break;
-    case 128: LBM_PAB(128); break;
-    default: LBM_PAB(256); break;
+    if (split) switch (tx) {
+        case 64: LBM_PAB(64, NQ >= 17); break;
+        case 128: LBM_PAB(128, NQ >= 17); break;
+        default: LBM_PAB(256, NQ >= 17); break;
+    }
+    else switch (tx) {
+        case 64: LBM_PAB(64, false); break;
+        case 128: LBM_PAB(128, false); break;
+        default: LBM_PAB(256, false); break;
     }
 #undef LBM_PAB
     return hipGetLastError();
