@@ -116,10 +116,12 @@ typedef struct {
  * the run's stream; 1 runs the boundary/PML chain on a side stream beside the bulk kernel (only
  * for a run that owns its stream; eager launches, no graphs); 2 launches phase A (characteristic
  * fill of the ring, PML Q update) and the bulk tiles as one grid, so they run beside the
- * streaming tiles (one stream, graphs and groups allowed); split places the phase-A blocks in
+ * streaming tiles (one stream, graphs and groups allowed), and takes FP64 and FP32 runs and groups
+ * with a large interior two steps per pass over it (layout 0; the last one or two steps of a call
+ * singly; debug poison and event timing take single steps); split places the phase-A blocks in
  * that grid: after split/8 of the bulk tiles (0..8, rounded down to a multiple of 8 blocks), or
  * -1 for the measured default (after all of the tiles when they outnumber the phase-A blocks
- * eightfold, as on large grids; else after half of them for D2Q37 in FP64, first otherwise).
+ * eightfold, as on large grids, and on small ones in FP64; else after half of them for D2Q37 in FP64, first otherwise).
  * Every schedule and placement gives the same bits.  Default {64, 4, 32, 2, -1}. */
 typedef struct {
     int32_t bulk_tx, bulk_ty;
@@ -296,7 +298,7 @@ lbm_status lbm_autotune(lbm_handle h, int32_t steps, const char *cache_path,
  * the frame kernel in ms[1].  mode 3: as mode 2 on every fourth step only (a sampled average that
  * leaves the other steps free of events).  The kernels' events are attached to their dispatch and
  * take the kernel's own start and end.  mode 0 turns timing off.  Any mode other than 0 makes
- * lbm_step launch eagerly (no graphs; the same kernel sequence); a mode outside 0..3 is
+ * lbm_step launch eagerly (no graphs) and take its steps one by one; a mode outside 0..3 is
  * LBM_ERR_ARG.  lbm_profile_read synchronises and returns the summed milliseconds and launch
  * counts since the last reset. */
 lbm_status lbm_profile(lbm_handle h, int enable);

@@ -1,6 +1,7 @@
 // HIP kernels (gfx950, wave64) for the thermal LBM with PML and open boundaries, compiled once
-// per velocity stencil: LBM_Q = 37 (default; this file) or 17 (lbm_kernels_d2q17.hip), each
-// instance in its own namespace (k37, k17) with its stencil's constants in scope.
+// per velocity stencil: LBM_Q = 37 (default; this file), 17 (lbm_kernels_d2q17.hip) or 9
+// (lbm_kernels_d2q9.hip), each instance in its own namespace (k37, k17, k9) with its stencil's
+// constants in scope.
 //
 // Every kernel takes an array of run descriptors, so one launch advances one run or a batch of
 // uneven runs.  Per step:
@@ -14,6 +15,12 @@
 //                  ZG copy, moments, U^{n+1} strip write, BGK + Omega^PML
 //                                                             (eqs. PMLCOLL, zg-bc)
 //   k_bulk         interior nodes: branch-free pull + moments + BGK             (eq. lbe)
+// phase A and the bulk tiles may go out as one grid (k_phase_a_bulk), and a small set's boundary
+// launches split a node's populations over four waves (k_frame_split, k_small_step).  Large runs
+// take two steps per pass over their interior:
+//   k_core         interior nodes: both steps, the level between in LDS
+//   k_phase_a, k_frame<STEP_FIRST>    the boundary's first step, into the bands of the level between
+//   k_phase_a, k_frame<STEP_SECOND>   its second step, from the bands
 //   k_advance      end of a batch of steps: advance the step counters and buffer parities
 //                  (the step kernels of sub-step k of a batch use parity par + k)
 // The ring blocks come first in their launches (their float64 chains are the longest) and are
@@ -38,6 +45,7 @@
 //   H = E0(s) + a^2/2 + a (O1(s) + a^2/6),  E0 = k0 + theta s/2,  k0 = 1 - b/2 - theta,
 // with O1 and k1 as above; feq(U) - fbar = w (drho H0 + rho dH) with dH = H(U) - H(U0)
 // expanded in products of deviations.
+// FP64 storage evaluates the same deviation as a polynomial in e (EqPoly).
 #include <type_traits>
 #include <utility>
 
@@ -2124,24 +2132,32 @@ __global__ __launch_bounds__(256) void k_phase_a(RunDev *const *__restrict__ run
 // frame kernel then reads.  nA and h are multiples of 8, so every block keeps its XCD map.  Both
 // paths share one register budget, held at 4 waves per SIMD (128 VGPRs) by the low-register
 // boundary code, the branch-light block dispatch and the occupancy target.
-// SPLIT: the phase-A blocks are those of phase_a_split, whose waves run alone or in twos on a SIMD and
-// take up to 256 VGPRs (at 128 they spill: 340^2 D2Q37 FP64 29.2 us against 20.4).
-template <class S, int TX, bool SPLIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT ? 2 : 4))) void k_phase_a_bulk(RunDev *const *__restrict__ runs,
+template <class S, int TX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_phase_a_bulk(RunDev *const *__restrict__ runs,
                                                       const int *__restrict__ preA, int nA,
                                                       const int *__restrict__ preB, int nB, int h,
                                                       int nruns, Sub ks) {
     const int b = blockIdx.x;
     const int pa = b - h;   // blocks [h, h + nA) are phase A; the tiles before and after them
-#if LBM_Q >= 17
-    if constexpr (SPLIT) {
-        __shared__ typename Traits<S>::C lds[NQ * SPLIT_BLOCK];
-        if ((unsigned)pa < (unsigned)nA) return phase_a_split<S, SRC_F>(runs, preA, nruns, ks, pa, lds);
-    }
-#endif
     if ((unsigned)pa < (unsigned)nA) phase_a_block<S, SRC_F>(runs, preA, nruns, ks, pa);
     else bulk_tile<S, TX>(runs, preB, nruns, ks, xcd_swizzle(pa < 0 ? b : b - nA, nB));
 }
+
+#if LBM_Q >= 17
+// The same grid for small sets, with the phase-A blocks of phase_a_split.  Its waves run alone or in
+// twos on a SIMD and take up to 256 VGPRs (at 128 they spill: 340^2 D2Q37 FP64 29.2 us against 20.4).
+template <class S, int TX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_small_step(RunDev *const *__restrict__ runs,
+                                                      const int *__restrict__ preA, int nA,
+                                                      const int *__restrict__ preB, int nB, int h,
+                                                      int nruns, Sub ks) {
+    __shared__ typename Traits<S>::C lds[NQ * SPLIT_BLOCK];
+    const int b = blockIdx.x;
+    const int pa = b - h;
+    if ((unsigned)pa < (unsigned)nA) phase_a_split<S, SRC_F>(runs, preA, nruns, ks, pa, lds);
+    else bulk_tile<S, TX>(runs, preB, nruns, ks, xcd_swizzle(pa < 0 ? b : b - nA, nB));
+}
+#endif
 
 // End of a batch of n steps in which the population buffers changed roles `flips` times: each run
 // advances by the sub-steps it was active for, min(n, limit - step).  A run's limit never falls
@@ -2497,21 +2513,26 @@ static hipError_t launch_phase_a_bulk(const LaunchSet &L, int storage, int tx, S
                   : nB >= 8 * nA || (split && storage == ST_F64) ? nB & ~7
                   : (NQ == 37 && storage == ST_F64) ? (nB / 2) & ~7 : 0;
     const int *pa = L.prefix[split ? CLS_A_SPLIT : CLS_A], *pb = L.prefix[CLS_BULK];
-#define LBM_PAB(TXV, SP)                                                                               \
-    LBM_DISPATCH(storage, if (a) hipExtLaunchKernelGGL((k_phase_a_bulk<S, TXV, SP>), dim3(nA + nB), dim3(256), \
+#define LBM_PAB(KERNEL, TXV)                                                                               \
+    LBM_DISPATCH(storage, if (a) hipExtLaunchKernelGGL((KERNEL<S, TXV>), dim3(nA + nB), dim3(256), \
                                                        0, s, a, b, 0, L.runs, pa, nA, pb, nB, h,   \
                                                        L.nruns, ks);                               \
-                          else hipLaunchKernelGGL((k_phase_a_bulk<S, TXV, SP>), dim3(nA + nB), dim3(256), \
+                          else hipLaunchKernelGGL((KERNEL<S, TXV>), dim3(nA + nB), dim3(256), \
                                                   0, s, L.runs, pa, nA, pb, nB, h, L.nruns, ks))
-    if (split) switch (tx) {
-        case 64: LBM_PAB(64, NQ >= 17); break;
-        case 128: LBM_PAB(128, NQ >= 17); break;
-        default: LBM_PAB(256, NQ >= 17); break;
+#if LBM_Q >= 17
+    if (split) {
+        switch (tx) {
+        case 64: LBM_PAB(k_small_step, 64); break;
+        case 128: LBM_PAB(k_small_step, 128); break;
+        default: LBM_PAB(k_small_step, 256); break;
+        }
+        return hipGetLastError();
     }
-    else switch (tx) {
-        case 64: LBM_PAB(64, false); break;
-        case 128: LBM_PAB(128, false); break;
-        default: LBM_PAB(256, false); break;
+#endif
+    switch (tx) {
+    case 64: LBM_PAB(k_phase_a_bulk, 64); break;
+    case 128: LBM_PAB(k_phase_a_bulk, 128); break;
+    default: LBM_PAB(k_phase_a_bulk, 256); break;
     }
 #undef LBM_PAB
     return hipGetLastError();
