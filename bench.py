@@ -55,15 +55,21 @@ def run_from_spec(lbm, spec, storage, stream=None, alloc=None, layout=0, bulk_tx
     return r
 
 
+# Steps of the pass that carries events, after the timed one.
+EVENT_STEPS = 256
+
+
 def time_run(torch, r, steps, warmup, mode):
-    """Time `steps` steps after `warmup`.  mode 3: the configured schedule with HIP events attached
-    to the dispatch of the step grid (the fused phase-A + bulk grid, or the bulk kernel) and of
-    the frame kernel on every fourth step (a sampled average; the other steps carry no events).
-    mode 1: the kernel classes in order, events on each class."""
+    """Time `steps` steps after `warmup`.  mode 3: the configured schedule as a user runs it, without
+    events; then up to EVENT_STEPS more steps with HIP events attached to the dispatch of the step
+    grid (the fused phase-A + bulk grid, or the bulk kernel) and of the frame kernel on every fourth
+    (under events a run takes its steps one by one, also where it would take two per pass).  mode
+    1: the kernel classes in order, events on each class, in the timed steps."""
     r.profile(0)
     r.step(warmup)
     r.synchronize()
-    r.profile(mode)
+    events = mode == 3
+    r.profile(0 if events else mode)
     r.profile_read(reset=True)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -71,6 +77,10 @@ def time_run(torch, r, steps, warmup, mode):
     r.synchronize()
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
+    if events:
+        r.profile(mode)
+        r.step(min(steps, EVENT_STEPS))
+        r.synchronize()
     ms, n = r.profile_read(reset=True)
     r.profile(0)
     return dt, ms, n
@@ -108,7 +118,7 @@ def kernel_bytes(storage, q, n_bulk, n_frame, n_q, fused=True):
 
 
 def measure(torch, lbm, r, spec, storage, steps, warmup, prof_steps, fused=True):
-    """Timed pass (the configured schedule, HIP events on a sample of steps) and, if prof_steps,
+    """Timed pass (the configured schedule), a pass with HIP events on a sample of steps and, if prof_steps,
     an in-order pass with per-class events.  Returns the result dict of one run."""
     Nx, Ny = r.grid()
     n_bulk, n_frame, n_q, n_ring = r.node_classes()
@@ -605,8 +615,9 @@ def roofline_entry(R, args, storage, copy_gbs):
         "device_copy_gbs": round(copy_gbs, 1) if copy_gbs else None,
         "frac_of_device_copy": round(gbs / copy_gbs, 4) if copy_gbs and gbs else None,
         "timing": "HIP events attached to the dispatch of the step grid and of the frame kernel "
-                  "(hipExtLaunchKernelGGL) on every fourth of the timed %d steps (%d launches each), "
-                  "on the stream they run on" % (args.steps, R["launches_timed"]),
+                  "(hipExtLaunchKernelGGL) on every fourth of %d further steps, taken one by one, after "
+                  "the timed %d (%d launches each), on the stream they run on"
+                  % (min(args.steps, EVENT_STEPS), args.steps, R["launches_timed"]),
     }
 
 
