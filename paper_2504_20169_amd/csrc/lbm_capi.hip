@@ -712,7 +712,8 @@ struct Stepper {
 
     lbm_status run(Batch b) {
         if (b.steps() == 0) return LBM_OK;
-        if (whole > 0 && b.steps() + 1 >= whole && !graphs.failed) {
+        // a whole batch, or the closing one of pairs up to an odd count, which is a step short of it
+        if (whole > 0 && b.steps() + (b.twos > 0) >= whole && !graphs.failed) {
             for (auto &i : graphs.items)
                 if (i.b.twos == b.twos && i.b.ones == b.ones) {
                     HIP_TRY(hipGraphLaunch(i.x, s));
