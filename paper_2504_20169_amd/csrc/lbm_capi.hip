@@ -1327,7 +1327,14 @@ lbm_status lbm_save(lbm_handle h, const char *path) {
     size_t gb = R.ring_n > 0 ? (size_t)h->lat->q * R.rplane * compute_size(storage) : 0;
     std::vector<char> buf(2 * fb + qb + 2 * ub + gb);
     char *p = buf.data();
-    for (int b = 0; b < 2; ++b) { HIP_TRY(hipMemcpy(p, R.f[b], fb, hipMemcpyDeviceToHost)); p += fb; }
+    // The moment strips alternate every step and the populations every pass, which may be two steps.
+    // The file has both by the step's parity, the current level first at even steps, so that a build
+    // which keeps one parity for both reads the right strip.
+    const int par = (int)(h->steps & 1);
+    for (int b = 0; b < 2; ++b) {
+        HIP_TRY(hipMemcpy(p, R.f[b ^ par ^ R.par], fb, hipMemcpyDeviceToHost));
+        p += fb;
+    }
     if (qb) { HIP_TRY(hipMemcpy(p, R.Q, qb, hipMemcpyDeviceToHost)); p += qb; }
     for (int b = 0; b < 2; ++b) { HIP_TRY(hipMemcpy(p, R.U[b], ub, hipMemcpyDeviceToHost)); p += ub; }
     if (gb) { HIP_TRY(hipMemcpy(p, R.G, gb, hipMemcpyDeviceToHost)); p += gb; }
@@ -1336,7 +1343,7 @@ lbm_status lbm_save(lbm_handle h, const char *path) {
     hdr.version = 5; hdr.Nx = R.Nx; hdr.Ny = R.Ny; hdr.storage = storage; hdr.W = h->W;
     hdr.layout = h->desc.layout; hdr.lattice = h->lat->q; hdr.pml_terms = (int32_t)h->pml_terms;
     for (int s = 0; s < 4; ++s) { hdr.pml[s] = h->pml[s]; hdr.bc[s] = h->bc[s]; }
-    hdr.par = R.par; hdr.steps = h->steps; hdr.plane = R.plane; hdr.qplane = R.qplane;
+    hdr.par = par; hdr.steps = h->steps; hdr.plane = R.plane; hdr.qplane = R.qplane;
     hdr.tau = h->desc.tau; hdr.rho0 = h->desc.rho0; hdr.ux0 = h->desc.ux0; hdr.uy0 = h->desc.uy0;
     hdr.T0 = h->desc.T0; hdr.sigma_max = h->sigma_max; hdr.scale = R.scale;
     hdr.checksum = fnv1a(buf.data(), buf.size(), 1469598103934665603ULL);
