@@ -7,6 +7,7 @@
 #include <array>
 #include <cmath>
 #include <cstdarg>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -71,7 +72,10 @@ struct DeviceMem {
         void *p = nullptr;
         bytes = (size_t)round_up((long long)std::max<size_t>(bytes, 256), 256);
         if (alloc && alloc->alloc) p = alloc->alloc(bytes, alloc->ctx);
-        else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
+        else if (hipMalloc(&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();   // it stays until it is read; the next launch would report it
+            p = nullptr;
+        }
         if (p) { ptrs.push_back(p); sizes.push_back(bytes); }
         return p;
     }
@@ -192,6 +196,7 @@ struct lbm_run {
     int *dprefix = nullptr;   // [NCLS][2] prefix arrays of the single-run launch set
     int nblocks[NCLS] = {};
     int core_rows = 0;        // rows of a two-step tile; 0: single steps only
+    bool no_bands = false;    // its two-step bands made room for another buffer: none any more
     const LatticeInfo *lat = &LATTICE_D2Q37;   // velocity stencil
     const KernelSet *ks = &k37::kernels;       // its kernels
     double fbar[NQ_MAX];
@@ -210,7 +215,6 @@ struct lbm_run {
     double prof_ms[3] = {0, 0, 0};
     int64_t prof_n[3] = {0, 0, 0};
     lbm_group *group = nullptr;
-    size_t footprint = 0;
     int *dflag = nullptr;             // lbm_check's flag, allocated with the run
     HostStage stage;
     unsigned debug = 0;               // lbm_set_debug flags
@@ -461,18 +465,26 @@ void set_scale(RunDev &R, double s) {
     R.scale_f = (float)s; R.inv_scale_f = (float)(1.0 / s);
 }
 
-size_t footprint_of(const RunDev &R, int storage, int nq) {
-    size_t b = 2 * (size_t)R.fsize * elem_size(storage) + (size_t)R.msize * elem_size(storage);
+// Whether the run by itself is taken in pairs (given its bands).
+bool pairs_alone(const RunDev &R, int storage) {
+    return R.core_strips > 0 &&
+           two_steps_pay(storage, (long long)(R.fx1 - R.fx0) * (R.fy1 - R.fy0), R.frame_n);
+}
+
+// bands: the run by itself has the two-step bands.
+size_t footprint_of(const RunDev &R, int storage, int nq, bool bands) {
+    size_t b = 2 * (size_t)R.fsize * elem_size(storage);
     if (R.has_q) b += (size_t)nq * R.qplane * compute_size(storage);
     b += 2 * 4 * (size_t)R.qplane * sizeof(double);
     if (R.ring_n > 0) b += (size_t)nq * R.rplane * compute_size(storage);
     if (R.tgt_pre && R.ring_n > 0) b += 4 * (size_t)R.rplane * sizeof(double);
     b += sizeof(RunDev) + 256 * 4 + nq * sizeof(double);
     // lbm_init_fields' transient staging of the four input fields (and, for FP16 storage, the
-    // per-block maxima that choose the scale): part of the peak while the run is set up
+    // per-block maxima that choose the scale): part of the peak while the run is set up.  The bands
+    // are taken after it is given back.
     const size_t nn = (size_t)R.Nx * R.Ny;
-    b += 4 * nn * sizeof(double) + (storage == ST_F16 ? ((nn + 255) / 256) * sizeof(float) + 256 : 0);
-    return b;
+    const size_t staging = 4 * nn * sizeof(double) + (storage == ST_F16 ? ((nn + 255) / 256) * sizeof(float) + 256 : 0);
+    return b + std::max(staging, bands ? (size_t)R.msize * elem_size(storage) : 0);
 }
 
 // Blocks of a run per launch class; rows: height of the two-step tiles (0: none).
@@ -493,24 +505,33 @@ void compute_blocks(const RunDev &R, int tx, int rows, int reach, int nb[NCLS]) 
     nb[CLS_FRAME2] = two ? rb + fb + (R.shell_n + FRAME_BLOCK - 1) / FRAME_BLOCK : 0;
 }
 
+// Whether a set of runs takes its steps in pairs, its members' bands aside.
+bool set_pairs(lbm_run *const *runs, size_t n) {
+    if (n == 0) return false;
+    long long interior = 0, frame = 0;
+    for (size_t k = 0; k < n; ++k) {
+        const RunDev &R = runs[k]->hd;
+        if (R.core_strips == 0 || runs[k]->no_bands) return false;
+        interior += (long long)(R.fx1 - R.fx0) * (R.fy1 - R.fy0);
+        frame += R.frame_n;
+    }
+    return two_steps_pay(runs[0]->desc.storage, interior, frame);
+}
+
 // Height of the two-step tiles of a set of runs: a tile of H rows forms H + 2 reach rows of the
 // level between, CORE_R per turn, and the device holds `slots` tiles at a time, so the time goes
 // as ceil(tiles / slots) times a tile's turns and half a turn to start; the H with the least.  0 if
 // the set takes single steps.
 int choose_core_rows(lbm_run *const *runs, size_t n) {
-    if (n == 0) return 0;
+    if (!set_pairs(runs, n)) return 0;
     const LatticeInfo &lt = *runs[0]->lat;
     const int reach = reach_of(lt);
     int tallest = 0;
-    long long interior = 0, frame = 0;
     for (size_t k = 0; k < n; ++k) {
         const RunDev &R = runs[k]->hd;
-        if (R.core_strips == 0 || !R.M) return 0;
-        interior += (long long)(R.fx1 - R.fx0) * (R.fy1 - R.fy0);
-        frame += R.frame_n;
+        if (!R.M) return 0;
         tallest = std::max(tallest, R.fy1 - R.fy0 - 2 * reach);
     }
-    if (!two_steps_pay(runs[0]->desc.storage, interior, frame)) return 0;
     const long long slots = 256 * (long long)core_tiles_per_cu(lt, (int)elem_size(runs[0]->desc.storage));
     long long best = -1;
     int best_h = 0;
@@ -537,6 +558,41 @@ lbm_status upload_prefix(lbm_run *h) {
     HIP_TRY(hipMemcpyAsync(h->dprefix, pre, sizeof pre, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     return LBM_OK;
+}
+
+// The two-step bands of a run: taken once a set that it is in takes its steps in pairs, after all
+// else, and given back when it is in none or when another buffer finds no memory.  Without them the
+// run takes single steps, whose bits are the same.  The run's stream is idle.
+lbm_status set_bands(lbm_run *h, void *M) {
+    h->hd.M = M;
+    HIP_TRY(hipMemcpyAsync((char *)h->dd + offsetof(RunDev, M), &h->hd.M, sizeof(void *), hipMemcpyHostToDevice, h->stream));
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    return LBM_OK;
+}
+lbm_status take_bands(lbm_run *h) {
+    if (h->hd.M) return LBM_OK;
+    void *M = h->mem.get((size_t)h->hd.msize * elem_size(h->desc.storage));
+    if (!M) return LBM_OK;
+    if (h->mem.overlapping()) return fail(LBM_ERR_ARG, "device buffers overlap: the allocator returned aliasing memory");
+    return set_bands(h, M);
+}
+lbm_status drop_bands(lbm_run *h) {
+    void *M = h->hd.M;
+    if (!M) return LBM_OK;
+    lbm_status st = set_bands(h, nullptr);
+    if (st == LBM_OK) h->mem.put(M);
+    return st;
+}
+
+// Device scratch of a call; if there is none, the run's bands make room for it.
+void *scratch_of(lbm_run *h, size_t bytes) {
+    void *p = h->mem.get(bytes);
+    if (p || !h->hd.M || hipStreamSynchronize(h->stream) != hipSuccess) return p;
+    h->no_bands = true;
+    h->graphs.drop();
+    if (h->group) h->group->dirty = true;
+    if (drop_bands(h) != LBM_OK || upload_prefix(h) != LBM_OK) return nullptr;
+    return h->mem.get(bytes);
 }
 
 // Whether a set's boundary leaves the device so idle that its launches split each node's populations
@@ -891,7 +947,7 @@ lbm_status lbm_footprint(lbm_handle h, size_t *bytes) {
     RunDev R{};
     lbm_status st = setup_geometry(h, R);
     if (st != LBM_OK) return st;
-    *bytes = footprint_of(R, h->desc.storage, h->lat->q);
+    *bytes = footprint_of(R, h->desc.storage, h->lat->q, pairs_alone(R, h->desc.storage) && (!h->inited || h->hd.M));
     return LBM_OK;
 }
 
@@ -935,7 +991,6 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
     }
     const int storage = h->desc.storage;
     const size_t es = elem_size(storage), cs = compute_size(storage);
-    h->footprint = footprint_of(R, storage, h->lat->q);
     for (int b = 0; b < 2; ++b) {
         R.f[b] = h->mem.get((size_t)R.fsize * es);
         R.U[b] = (double *)h->mem.get(4 * (size_t)R.qplane * sizeof(double));
@@ -943,8 +998,7 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
     }
     R.Q = R.has_q ? h->mem.get((size_t)h->lat->q * R.qplane * cs) : nullptr;
     R.G = R.ring_n > 0 ? h->mem.get((size_t)h->lat->q * R.rplane * cs) : nullptr;
-    // without the bands the run takes single steps
-    R.M = R.msize > 0 ? h->mem.get((size_t)R.msize * es) : nullptr;
+    R.M = nullptr;
     const bool need_p = R.tgt_pre && R.ring_n > 0;
     R.P = need_p ? (double *)h->mem.get(4 * (size_t)R.rplane * sizeof(double)) : nullptr;
     h->dd = (RunDev *)h->mem.get(sizeof(RunDev));
@@ -1008,6 +1062,10 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
                         nullptr, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     h->mem.put(dfield);
+    if (pairs_alone(h->hd, storage) && (st = take_bands(h)) != LBM_OK) {
+        h->mem.release_all();
+        return st;
+    }
     lbm_status ps = upload_prefix(h);
     if (ps != LBM_OK) return ps;
     h->inited = true;
@@ -1087,7 +1145,7 @@ lbm_status lbm_moments(lbm_handle h, double *rho, double *ux, double *uy, double
         HIP_TRY(h->ks->moments(h->dd, h->desc.storage, R.Nx, R.Ny, rho, ux, uy, T, h->stream));
         return LBM_OK;
     }
-    double *tmp = (double *)h->mem.get(4 * nn * sizeof(double));
+    double *tmp = (double *)scratch_of(h, 4 * nn * sizeof(double));
     if (!tmp) return fail(LBM_ERR_OOM, "device allocation failed");
     double *d[4] = {tmp, tmp + nn, tmp + 2 * nn, tmp + 3 * nn};
     double *o[4] = {rho, ux, uy, T};
@@ -1114,7 +1172,7 @@ lbm_status lbm_populations(lbm_handle h, double *f) {
     if (!h->inited) return fail(LBM_ERR_STATE, "not initialised");
     const RunDev &R = h->hd;
     const size_t n = (size_t)h->lat->q * R.Nx * R.Ny;
-    double *tmp = (double *)h->mem.get(n * sizeof(double));
+    double *tmp = (double *)scratch_of(h, n * sizeof(double));
     if (!tmp) return fail(LBM_ERR_OOM, "device allocation failed");
     hipError_t e = h->ks->export_f(h->dd, h->desc.storage, R.Nx, R.Ny, h->fbar_d, tmp, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(f, tmp, n * sizeof(double), hipMemcpyDeviceToHost, h->stream);
@@ -1130,7 +1188,7 @@ lbm_status lbm_pml_q(lbm_handle h, double *Q) {
     const RunDev &R = h->hd;
     const size_t n = (size_t)h->lat->q * R.Nx * R.Ny;
     if (!R.has_q) { std::memset(Q, 0, n * sizeof(double)); return LBM_OK; }
-    double *tmp = (double *)h->mem.get(n * sizeof(double));
+    double *tmp = (double *)scratch_of(h, n * sizeof(double));
     if (!tmp) return fail(LBM_ERR_OOM, "device allocation failed");
     hipError_t e = hipMemsetAsync(tmp, 0, n * sizeof(double), h->stream);
     if (e == hipSuccess) e = h->ks->export_q(h->dd, h->desc.storage, R.ann0 + R.ann_n, tmp, h->stream);
@@ -1148,7 +1206,7 @@ lbm_status lbm_error_norms(lbm_handle h, const double *ref_rho, const double *re
     const RunDev &R = h->hd;
     const size_t nn = (size_t)R.Nx * R.Ny, nb = (size_t)h->desc.nx * h->desc.ny;
     const int ly = h->desc.ny;
-    double *tmp = (double *)h->mem.get((3 * nn + 3 * nb + 3 * (size_t)ly + 3) * sizeof(double));
+    double *tmp = (double *)scratch_of(h, (3 * nn + 3 * nb + 3 * (size_t)ly + 3) * sizeof(double));
     if (!tmp) return fail(LBM_ERR_OOM, "device allocation failed");
     double *m = tmp, *refs = tmp + 3 * nn, *part = refs + 3 * nb, *dout = part + 3 * (size_t)ly;
     hipError_t e = h->ks->moments(h->dd, h->desc.storage, R.Nx, R.Ny, m, m + nn, nullptr, m + 2 * nn, h->stream);
@@ -1529,6 +1587,10 @@ lbm_status lbm_group_remove(lbm_group_handle g, lbm_handle h) {
     auto it = std::find(g->members.begin(), g->members.end(), h);
     if (it == g->members.end()) return fail(LBM_ERR_ARG, "run is not in this group");
     HIP_TRY(hipStreamSynchronize(g->stream));
+    if (!pairs_alone(h->hd, h->desc.storage)) {
+        lbm_status st = drop_bands(h);
+        if (st != LBM_OK) return st;
+    }
     g->members.erase(it);
     h->group = nullptr;
     h->stream = h->own_stream ? h->own_stream : (hipStream_t)h->desc.stream;
@@ -1567,7 +1629,20 @@ static lbm_status group_rebuild(lbm_group *g) {
     std::vector<RunDev *> ptrs(n);
     std::vector<int> pre(NCLS * (g->cap + 1), 0);
     int tot[NCLS] = {};
+    // bands for a group that takes pairs; members that have them for no use go without
+    if (set_pairs(g->members.data(), n))
+        for (lbm_run *h : g->members) {
+            lbm_status st = take_bands(h);
+            if (st != LBM_OK) return st;
+            if (!h->hd.M) break;
+        }
     g->core_rows = choose_core_rows(g->members.data(), n);
+    if (g->core_rows == 0)
+        for (lbm_run *h : g->members)
+            if (!pairs_alone(h->hd, h->desc.storage)) {
+                lbm_status st = drop_bands(h);
+                if (st != LBM_OK) return st;
+            }
     for (size_t k = 0; k < n; ++k) {
         lbm_run *h = g->members[k];
         ptrs[k] = h->dd;
@@ -1763,6 +1838,7 @@ void lbm_group_destroy(lbm_group_handle g) {
     if (!g) return;
     (void)hipStreamSynchronize(g->stream);
     for (lbm_run *h : g->members) {
+        if (!pairs_alone(h->hd, h->desc.storage)) (void)drop_bands(h);
         h->group = nullptr;
         h->stream = h->own_stream ? h->own_stream : (hipStream_t)h->desc.stream;
     }

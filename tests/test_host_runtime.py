@@ -1,0 +1,119 @@
+"""The library's host side on the CPU, under a stand-in for the HIP runtime (tests/host/fake_hip.cpp)
+that counts memory and logs launches, copies and graphs instead of running kernels: what it does
+when device memory runs out."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from paper_2504_20169_amd import lbm
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists(lbm.LIB_PATH),
+                                reason="g++ or the library is missing")
+
+PRELUDE = """
+import ctypes, sys
+sys.path.insert(0, %r)
+import numpy as np
+from paper_2504_20169_amd import lbm
+F = ctypes.CDLL(%r)
+F.fake_log.restype = ctypes.c_char_p
+F.fake_used.restype = F.fake_pinned.restype = ctypes.c_size_t
+F.fake_limit.argtypes = [ctypes.c_size_t]
+F.fake_refuse.argtypes = [ctypes.c_size_t, ctypes.c_size_t]
+log = lambda: F.fake_log().decode().split("\\n")
+def run(nx, ny, W=0, bc="periodic", **kw):
+    r = lbm.Run(nx, ny, 0.8, **kw)
+    r.set_bc(15, bc)
+    if W:
+        r.set_pml(15, W, 0.01)
+    return r
+def init(r):
+    r.init(1.0, 0.0, 0.0, 1.0)
+    return r
+def pairs(n=8, of=None):
+    log()
+    (of.step(nsteps=n) if isinstance(of, lbm.Group) else of.step(n))
+    return sum("k_core" in l for l in log())
+"""
+
+
+@pytest.fixture(scope="session")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "host", "fake_hip.cpp")],
+                   check=True)
+    return so
+
+
+def _play(fake, code):
+    res = subprocess.run([sys.executable, "-c", PRELUDE % (ROOT, fake) + code + "\nprint('played')"],
+                         env=dict(os.environ, LD_PRELOAD=fake), capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0 and res.stdout.endswith("played\n"), res.stdout[-1500:] + res.stderr[-3000:]
+
+
+def test_bands_are_taken_last_and_only_where_pairs_are(fake):
+    """A run that pairs alone holds bands, one that does not holds what its footprint without them
+    says; with memory for all but the bands it initialises, takes single steps, and later calls see
+    no error of the refused allocation."""
+    _play(fake, """
+a = init(run(6500, 103, W=4, bc="zg"))
+with_bands = F.fake_used()
+assert pairs(of=a) == 3 and a.footprint() + 8192 >= with_bands
+a.close()
+assert F.fake_used() == 0
+r = run(6500, 103, W=4, bc="zg")
+peak = r.footprint()
+F.fake_limit(with_bands - 1)         # the staging of the fields is less than the bands
+r.init(1.0, 0.0, 0.0, 1.0)
+assert r.footprint() < peak and F.fake_used() < with_bands
+assert pairs(of=r) == 0
+r.close()
+F.fake_limit(1 << 62)
+b = init(run(1024, 1024, W=32, bc="nrbc", storage="f32"))     # no pairs by itself
+assert F.fake_used() <= b.footprint() - 4 * 8 * 1088 * 1088 + 8192
+assert pairs(of=b) == 0
+""")
+
+
+def test_a_result_makes_bands_give_way(fake):
+    """Device scratch of a call that finds no memory takes that of the bands: what fitted without
+    them still does."""
+    _play(fake, """
+a = init(run(6500, 103, W=4, bc="zg"))
+assert pairs(of=a) == 3
+F.fake_limit(F.fake_used())          # nothing left
+a.moments()
+assert pairs(of=a) == 0 and a.footprint() >= F.fake_used()
+a.moments()
+""")
+
+
+def test_bands_of_a_group(fake):
+    """Members that do not pair alone hold bands while they are in a group that does, and none after;
+    if one of them finds no memory for its bands the group takes single steps."""
+    _play(fake, """
+big = init(run(720, 700, lattice=9))
+small = init(run(120, 110, lattice=9))
+alone = F.fake_used()
+g = lbm.Group()
+g.add(big); g.add(small)
+assert pairs(of=g) == 3 and F.fake_used() > alone
+assert pairs(of=g) == 3
+held = F.fake_used()
+g.remove(small)
+assert F.fake_used() < held and pairs(of=g) == 3
+g.add(small)
+F.fake_refuse(20000, 1 << 62)        # no more bands
+assert pairs(of=g) == 0
+F.fake_refuse(1 << 62, 1 << 62)
+g.remove(small); g.add(small)
+assert pairs(of=g) == 3
+g.close()
+assert pairs(of=big) == 3 and pairs(of=small) == 0
+""")
