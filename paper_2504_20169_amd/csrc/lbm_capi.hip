@@ -927,6 +927,7 @@ lbm_status lbm_set_debug(lbm_handle h, unsigned flags) {
     if (!h) return fail(LBM_ERR_ARG, "NULL handle");
     if (flags & ~(unsigned)(LBM_DEBUG_POISON | LBM_DEBUG_RANGES)) return fail(LBM_ERR_ARG, "unknown debug flag");
     if (h->debug == flags) return LBM_OK;
+    if (h->inited) HIP_TRY(hipStreamSynchronize(h->stream));   // a graph of the old flags may be running
     h->debug = flags;
     h->graphs.drop();                    // captured steps are recaptured with the new flags
     if (h->group) h->group->dirty = true;
@@ -1316,7 +1317,12 @@ lbm_status lbm_set_launch(lbm_handle h, const lbm_launch *cfg) {
     if (cfg->overlap < 0 || cfg->overlap > 2) return fail(LBM_ERR_ARG, "overlap must be 0, 1 or 2");
     if (cfg->split < -1 || cfg->split > 8) return fail(LBM_ERR_ARG, "split must be -1 or 0..8");
     if (h->group) return fail(LBM_ERR_STATE, "run is in a group");
-    h->graphs.drop();   // step graphs hold the old configuration
+    const lbm_launch &old = h->launch;
+    if (cfg->bulk_tx != old.bulk_tx || cfg->graph_steps != old.graph_steps || cfg->overlap != old.overlap ||
+        cfg->split != old.split) {       // step graphs hold the old configuration
+        if (h->inited) HIP_TRY(hipStreamSynchronize(h->stream));
+        h->graphs.drop();
+    }
     h->launch = *cfg;
     if (h->inited) return upload_prefix(h);
     return LBM_OK;

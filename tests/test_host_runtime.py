@@ -1,6 +1,6 @@
 """The library's host side on the CPU, under a stand-in for the HIP runtime (tests/host/fake_hip.cpp)
 that counts memory and logs launches, copies and graphs instead of running kernels: what it does
-when device memory runs out."""
+when device memory runs out, and that it waits before it frees."""
 import os
 import shutil
 import subprocess
@@ -116,4 +116,34 @@ g.remove(small); g.add(small)
 assert pairs(of=g) == 3
 g.close()
 assert pairs(of=big) == 3 and pairs(of=small) == 0
+""")
+
+
+def test_graphs_are_destroyed_when_they_are_done(fake):
+    """A new launch configuration or debug flag drops the captured steps once those in flight have
+    ended, on the run's stream; the same configuration keeps them."""
+    _play(fake, """
+for kw, nx in (({}, 64), (dict(lattice=9), 700)):
+    r = init(run(nx, nx, **kw))
+    for change in (lambda: r.set_launch(bulk_tx=128), lambda: r.set_launch(bulk_tx=128, split=2),
+                   lambda: r.set_launch(graph_steps=16), lambda: r.set_debug(lbm.LBM_DEBUG_RANGES),
+                   lambda: r.set_debug(0), r.close):
+        r.step(70)
+        assert "instantiate" in log()
+        change()
+        assert "GRAPH DESTROYED IN FLIGHT" not in log(), change
+r = init(run(64, 64))
+r.step(70)
+log()
+r.set_launch()
+r.step(70)
+assert "instantiate" not in log()
+g = lbm.Group()
+g.add(r)
+g.step(nsteps=70)
+g.set_launch(bulk_tx=256)
+g.step(nsteps=70)
+g.remove(r)
+g.close()
+assert "GRAPH DESTROYED IN FLIGHT" not in log()
 """)
