@@ -465,10 +465,15 @@ void set_scale(RunDev &R, double s) {
     R.scale_f = (float)s; R.inv_scale_f = (float)(1.0 / s);
 }
 
+// Interior nodes of a run (none where the frame covers the grid).
+long long interior_of(const RunDev &R) {
+    return (long long)std::max(0, R.fx1 - R.fx0) * std::max(0, R.fy1 - R.fy0);
+}
+
 // Whether the run by itself is taken in pairs (given its bands).
 bool pairs_alone(const RunDev &R, int storage) {
     return R.core_strips > 0 &&
-           two_steps_pay(storage, (long long)(R.fx1 - R.fx0) * (R.fy1 - R.fy0), R.frame_n);
+           two_steps_pay(storage, interior_of(R), R.frame_n);
 }
 
 // bands: the run by itself has the two-step bands.
@@ -512,7 +517,7 @@ bool set_pairs(lbm_run *const *runs, size_t n) {
     for (size_t k = 0; k < n; ++k) {
         const RunDev &R = runs[k]->hd;
         if (R.core_strips == 0 || runs[k]->no_bands) return false;
-        interior += (long long)(R.fx1 - R.fx0) * (R.fy1 - R.fy0);
+        interior += interior_of(R);
         frame += R.frame_n;
     }
     return two_steps_pay(runs[0]->desc.storage, interior, frame);
@@ -597,8 +602,14 @@ void *scratch_of(lbm_run *h, size_t bytes) {
 
 // Whether a set's boundary leaves the device so idle that its launches split each node's populations
 // over four waves.
-bool split_small(const LaunchSet &L, const lbm_run *h) {
-    return L.blocks[CLS_SPLIT] <= split_most(h->lat->q, (int)elem_size(h->desc.storage));
+bool split_small(const LaunchSet &L, lbm_run *const *runs, size_t n) {
+    bool ring = false;
+    long long interior = 0;
+    for (size_t k = 0; k < n; ++k) {
+        ring = ring || runs[k]->hd.ring_n > 0;
+        interior += interior_of(runs[k]->hd);
+    }
+    return L.blocks[CLS_SPLIT] <= split_most(runs[0]->lat->q, (int)elem_size(runs[0]->desc.storage), ring, interior);
 }
 
 LaunchSet single_set(lbm_run *h) {
@@ -611,7 +622,7 @@ LaunchSet single_set(lbm_run *h) {
     }
     L.poison = (h->debug & LBM_DEBUG_POISON) ? 1 : 0;
     L.split = h->launch.split;
-    L.split_small = split_small(L, h);
+    L.split_small = split_small(L, &h, 1);
     L.core_rows = h->launch.overlap == 2 && !h->prof && !L.poison ? h->core_rows : 0;
     L.nruns = 1;
     return L;
@@ -1700,7 +1711,7 @@ lbm_status lbm_group_step(lbm_group_handle g, const int64_t *steps, int64_t nste
     L.nruns = (int)n;
     L.poison = g->poison;
     L.split = g->launch.split;
-    L.split_small = split_small(L, g->members[0]);
+    L.split_small = split_small(L, g->members.data(), n);
     L.core_rows = g->launch.overlap == 2 && !g->poison ? g->core_rows : 0;
     // Runs past their own count skip every kernel, so whole graphs of G batched steps serve any
     // mix of counts; the remainder is launched eagerly.

@@ -2508,9 +2508,12 @@ static hipError_t launch_phase_a_bulk(const LaunchSet &L, int storage, int tx, S
     // still outlasts its latency (1088^2 NRBC + PML: 178.5 against 185.5 us per step), and none
     // for the rest, where the shorter tiles would leave phase A on the tail (FP32 98.8 against
     // 97.1 us, FP16 66.6 against 62.0, D2Q9 FP64 47.1 against 46.5).  With split phase-A blocks all
-    // of them in FP64 (D2Q37 at 190^2: 12.5 us, with half 13.9; D2Q17 at 340^2: 11.5, with none 13.2).
+    // of them in FP64 (D2Q37 at 190^2: 12.5 us, with half 13.9; D2Q17 at 340^2: 11.5, with none
+    // 13.2) and none in FP32 and FP16, at any ratio (us per step with none and all: NRBC 500^2 with 4
+    // cells FP32 31.0, 33.9, 1000^2 72.4, 77.5; ZG 700^2 with 4 cells 42.5, 42.5).
     const int h = L.split >= 0 ? (nB * L.split / 8) & ~7
-                  : nB >= 8 * nA || (split && storage == ST_F64) ? nB & ~7
+                  : split ? (storage == ST_F64 ? nB & ~7 : 0)
+                  : nB >= 8 * nA ? nB & ~7
                   : (NQ == 37 && storage == ST_F64) ? (nB / 2) & ~7 : 0;
     const int *pa = L.prefix[split ? CLS_A_SPLIT : CLS_A], *pb = L.prefix[CLS_BULK];
 #define LBM_PAB(KERNEL, TXV)                                                                               \

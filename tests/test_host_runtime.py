@@ -1,6 +1,6 @@
 """The library's host side on the CPU, under a stand-in for the HIP runtime (tests/host/fake_hip.cpp)
 that counts memory and logs launches, copies and graphs instead of running kernels: what it does
-when device memory runs out, and that it waits before it frees."""
+when device memory runs out, that it waits before it frees, and which kernels a schedule has."""
 import os
 import shutil
 import subprocess
@@ -146,4 +146,29 @@ g.step(nsteps=70)
 g.remove(r)
 g.close()
 assert "GRAPH DESTROYED IN FLIGHT" not in log()
+""")
+
+
+def test_where_boundary_launches_split_a_node(fake):
+    """Single steps of thick frames around little interior take whole nodes unless a side is
+    characteristic; thin frames, and those of a large interior, are split over four waves."""
+    _play(fake, """
+for nx, ny, bx, by, W, storage, lattice, split in (
+        (591, 41, "periodic", "zg", 52, "f32", 37, False), (591, 41, "periodic", "nrbc", 52, "f32", 37, True),
+        (100, 100, "zg", "zg", 60, "f16", 37, False), (100, 100, "nrbc", "nrbc", 60, "f16", 37, True),
+        (156, 1183, "zg", "periodic", 15, "f32", 37, False), (350, 350, "zg", "zg", 20, "f32", 37, True),
+        (300, 80, "zg", "zg", 32, "f64", 17, False), (300, 80, "nrbc", "nrbc", 32, "f64", 17, True),
+        (300, 80, "zg", "zg", 32, "f64", 37, True), (156, 1183, "zg", "periodic", 15, "f64", 17, True), (500, 500, "zg", "zg", 20, "f32", 17, False),
+        (600, 600, "periodic", "periodic", 0, "f64", 37, True), (100, 100, "zg", "zg", 60, "f32", 9, False)):
+    r = lbm.Run(nx, ny, 0.8, storage=storage, lattice=lattice)
+    r.set_bc(3, bx); r.set_bc(12, by)
+    if W:
+        r.set_pml(3 * (bx != "periodic") | 12 * (by != "periodic"), W, 0.01)
+    init(r)
+    log()
+    r.step(2)
+    names = " ".join(log())
+    assert ("k_frame_split" in names, "k_small_step" in names) == (split, split), (nx, ny, bx, by, W, storage, lattice)
+    assert ("k_phase_a_bulk" in names) == (not split)
+    r.close()
 """)
