@@ -612,6 +612,14 @@ bool split_small(const LaunchSet &L, lbm_run *const *runs, size_t n) {
     return L.blocks[CLS_SPLIT] <= split_most(runs[0]->lat->q, (int)elem_size(runs[0]->desc.storage), ring, interior);
 }
 
+// Whether the frame kernel streams its stores (see frame_stream_most).
+bool stream_frame(lbm_run *const *runs, size_t n) {
+    const size_t es = elem_size(runs[0]->desc.storage);
+    size_t bytes = 0;
+    for (size_t k = 0; k < n; ++k) bytes += 2 * es * runs[k]->lat->q * runs[k]->hd.Nx * runs[k]->hd.Ny;
+    return es == 8 || bytes < frame_stream_most((int)es);
+}
+
 LaunchSet single_set(lbm_run *h) {
     LaunchSet L;
     L.ks = h->ks;
@@ -623,6 +631,7 @@ LaunchSet single_set(lbm_run *h) {
     L.poison = (h->debug & LBM_DEBUG_POISON) ? 1 : 0;
     L.split = h->launch.split;
     L.split_small = split_small(L, &h, 1);
+    L.stream_frame = stream_frame(&h, 1);
     L.core_rows = h->launch.overlap == 2 && !h->prof && !L.poison ? h->core_rows : 0;
     L.nruns = 1;
     return L;
@@ -1712,6 +1721,7 @@ lbm_status lbm_group_step(lbm_group_handle g, const int64_t *steps, int64_t nste
     L.poison = g->poison;
     L.split = g->launch.split;
     L.split_small = split_small(L, g->members.data(), n);
+    L.stream_frame = stream_frame(g->members.data(), n);
     L.core_rows = g->launch.overlap == 2 && !g->poison ? g->core_rows : 0;
     // Runs past their own count skip every kernel, so whole graphs of G batched steps serve any
     // mix of counts; the remainder is launched eagerly.

@@ -1388,17 +1388,16 @@ __global__ __launch_bounds__(256) void k_bulk(RunDev *const *__restrict__ runs,
 // stores): a handful of memory round trips per node instead of one per population.
 // With BANDS (first step of a two-step pass) the node is written to the bands instead of a buffer:
 // dnode in its band, and dnode2 if `two`, where it lies in both.
-template <class S, class C, bool BANDS, class Stride>
+template <class S, class C, bool BANDS, bool STREAM, class Stride>
 __device__ __forceinline__ void frame_collide(CRun &R, const K<C> &k, const C (&g)[NQ], int x, int y,
                                               int t, const GLOBAL C *__restrict__ Q,
                                               GLOBAL S *__restrict__ dnode, Stride plane,
                                               GLOBAL S *__restrict__ dnode2, Stride plane2, bool two,
                                               GLOBAL double *__restrict__ Un) {
-    // FP64 streams to a buffer, which is next read a whole step later.  The bands are read by the next
-    // kernel.  FP32 and FP16 rows of the side strips start and end inside 64-byte pieces, which the
-    // cache joins with their neighbours' before they go to memory (frame launch, streaming / ordinary
-    // stores: 1088^2 FP32 25.1 / 22.6 us, FP16 20.8 / 18.5, 4224^2 FP32 181 / 161; FP64 40.0 / 39.5
-    // and 295 / 298)
+    // FP64 streams to a buffer, which is next read a whole step later (frame launch, streaming /
+    // ordinary stores: 1088^2 40.0 / 39.5 us, 4224^2 295 / 298); FP32 and FP16 do so in small sets
+    // (1088^2 FP32 25.1 / 22.6, FP16 20.8 / 18.5, 4224^2 FP32 181 / 161; frame_stream_most has the
+    // small).  The bands are read by the next kernel.
     auto put = [&](auto ic, C out) {
         constexpr int i = decltype(ic)::value;
         const S v = cvt_out(out, k.scale, (S *)nullptr);
@@ -1406,7 +1405,7 @@ __device__ __forceinline__ void frame_collide(CRun &R, const K<C> &k, const C (&
             dnode[(Stride)i * plane] = v;
             if (two) dnode2[(Stride)i * plane2] = v;
         } else {
-            if constexpr (sizeof(S) == 8) __builtin_nontemporal_store(v, dnode + (long long)i * plane);
+            if constexpr (STREAM) __builtin_nontemporal_store(v, dnode + (long long)i * plane);
             else dnode[(long long)i * plane] = v;
         }
     };
@@ -1676,7 +1675,7 @@ __global__ __launch_bounds__(CORE_X *CORE_R, core_waves(LBM_INFO, (int)sizeof(S)
 // reads frame nodes of the first.
 enum { STEP_ONE = 0, STEP_FIRST = 1, STEP_SECOND = 2 };
 
-template <class S, int STEP>
+template <class S, int STEP, bool STREAM>
 __global__ __launch_bounds__(256) void k_frame(RunDev *const *__restrict__ runs,
                                                const int *__restrict__ prefix, int nruns, Sub ks) {
     using C = typename Traits<S>::C;
@@ -1727,10 +1726,10 @@ __global__ __launch_bounds__(256) void k_frame(RunDev *const *__restrict__ runs,
         const unsigned ca = (unsigned)R.l_first + (unsigned)(y - R.gym) * (unsigned)(NQ * R.l_row) +
                             (unsigned)band_col(R, x);
         const unsigned pa = (unsigned)(rows ? R.m_row : R.l_row);
-        frame_collide<S, C, true, unsigned>(R, k, g, x, y, t, Q, M + (rows ? ra : ca), pa, M + ca,
+        frame_collide<S, C, true, STREAM, unsigned>(R, k, g, x, y, t, Q, M + (rows ? ra : ca), pa, M + ca,
                                             (unsigned)R.l_row, rows && cols, Un);
     } else {
-        frame_collide<S, C, false, long long>(R, k, g, x, y, t, Q,
+        frame_collide<S, C, false, STREAM, long long>(R, k, g, x, y, t, Q,
                                               (GLOBAL S *)R.f[par ^ 1] + (long long)y * R.pitch + x,
                                               R.plane, (GLOBAL S *)nullptr, 0, false, Un);
     }
@@ -2468,10 +2467,19 @@ static hipError_t launch_frame(const LaunchSet &L, int storage, Sub ks, hipStrea
     const int nb = L.blocks[CLS_FRAME];
     if (nb <= 0) return hipSuccess;
     const int *pre = L.prefix[CLS_FRAME];
-    LBM_DISPATCH(storage, if (a) hipExtLaunchKernelGGL((k_frame<S, STEP_ONE>), dim3(nb), dim3(256), 0, s, a, b, 0,
-                                                       L.runs, pre, L.nruns, ks);
-                          else hipLaunchKernelGGL((k_frame<S, STEP_ONE>), dim3(nb), dim3(256), 0, s, L.runs, pre,
-                                                  L.nruns, ks));
+#define LBM_FRAME(STREAM)                                                                                  \
+    do {                                                                                                   \
+        if (a) hipExtLaunchKernelGGL((k_frame<S, STEP_ONE, STREAM>), dim3(nb), dim3(256), 0, s, a, b, 0,   \
+                                     L.runs, pre, L.nruns, ks);                                            \
+        else hipLaunchKernelGGL((k_frame<S, STEP_ONE, STREAM>), dim3(nb), dim3(256), 0, s, L.runs, pre,    \
+                                L.nruns, ks);                                                              \
+    } while (0)
+    if (L.stream_frame) {
+        LBM_DISPATCH(storage, LBM_FRAME(true));
+    } else {
+        LBM_DISPATCH(storage, LBM_FRAME(sizeof(S) == 8));
+    }
+#undef LBM_FRAME
     return hipGetLastError();
 }
 
@@ -2555,12 +2563,12 @@ static hipError_t two_steps(const LaunchSet &L, int storage, Sub k1, hipStream_t
     hipError_t e = launch_target(L, storage, k1, s);
     if (nA.x > 0)
         hipLaunchKernelGGL((k_phase_a<S, SRC_F>), nA, tb, 0, s, L.runs, L.prefix[CLS_A], L.nruns, k1);
-    hipLaunchKernelGGL((k_frame<S, STEP_FIRST>), dim3(L.blocks[CLS_FRAME]), tb, 0, s, L.runs,
+    hipLaunchKernelGGL((k_frame<S, STEP_FIRST, false>), dim3(L.blocks[CLS_FRAME]), tb, 0, s, L.runs,
                        L.prefix[CLS_FRAME], L.nruns, k1);
     if (e == hipSuccess) e = launch_target(L, storage, k2, s);
     if (nA.x > 0)
         hipLaunchKernelGGL((k_phase_a<S, SRC_M>), nA, tb, 0, s, L.runs, L.prefix[CLS_A], L.nruns, k2);
-    hipLaunchKernelGGL((k_frame<S, STEP_SECOND>), dim3(L.blocks[CLS_FRAME2]), tb, 0, s, L.runs,
+    hipLaunchKernelGGL((k_frame<S, STEP_SECOND, sizeof(S) == 8>), dim3(L.blocks[CLS_FRAME2]), tb, 0, s, L.runs,
                        L.prefix[CLS_FRAME2], L.nruns, k2);
     return e != hipSuccess ? e : hipGetLastError();
 }

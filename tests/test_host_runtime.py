@@ -172,3 +172,23 @@ for nx, ny, bx, by, W, storage, lattice, split in (
     assert ("k_phase_a_bulk" in names) == (not split)
     r.close()
 """)
+
+
+def test_frame_stores_stream_in_small_sets(fake):
+    """The whole-node frame kernel streams FP64 always, FP32 and FP16 while the population buffers of
+    the run or group stay small."""
+    _play(fake, """
+streams = lambda: "ELb1E" in [l for l in log() if "k_frame" in l][-1]
+for nx, ny, storage, lattice, want in ((65, 1311, "f32", 9, True), (700, 700, "f32", 9, True), (800, 800, "f32", 9, False), (900, 900, "f64", 9, True),
+                                       (500, 500, "f16", 9, True), (1100, 1100, "f16", 9, False)):
+    r = init(run(nx, ny, W=12, bc="nrbc", storage=storage, lattice=lattice))
+    r.step(1)
+    assert streams() == want, (nx, ny, storage)
+    r.close()
+g = lbm.Group()
+small = [init(run(200, 200, W=12, bc="nrbc", storage="f32", lattice=9)) for _ in range(16)]
+for k, r in enumerate(small):
+    g.add(r)
+    g.step(nsteps=1)
+    assert streams() == (k < 13), k
+""")
