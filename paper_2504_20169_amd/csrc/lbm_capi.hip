@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstddef>
@@ -108,12 +109,13 @@ struct DeviceMem {
     }
 };
 
-// Pinned host memory of one run for what a call brings to or from the host, kept up to MOST bytes.  A
-// small pageable copy costs about 20 us whatever its size (four fields of a 220 x 20 grid: 58 us, as
-// one pinned copy 9-13 us); from a megabyte on the two are even.  Every call that uses it drains
-// the run's stream before it returns.
+// Pinned host memory of one run for what a call brings to or from the host, kept up to MOST bytes, and
+// up to ALL bytes by the runs of the process together.  A small pageable copy costs about 20 us
+// whatever its size (four fields of a 220 x 20 grid: 58 us, as one pinned copy 9-13 us); from a
+// megabyte on the two are even.  Every call that uses it drains the run's stream before it returns.
+std::atomic<size_t> pinned_bytes{0};
 struct HostStage {
-    static constexpr size_t MOST = 1 << 20;
+    static constexpr size_t MOST = 1 << 20, ALL = 64 * MOST;
     void *p = nullptr;
     size_t cap = 0;
     // at least `bytes` of pinned memory, or NULL: the caller then copies to pageable memory
@@ -122,8 +124,13 @@ struct HostStage {
         if (bytes > cap) {
             release();
             const size_t want = std::max<size_t>((size_t)round_up((long long)bytes, 4096), 4096);
+            if (pinned_bytes.fetch_add(want) + want > ALL) {
+                pinned_bytes -= want;
+                return nullptr;
+            }
             if (hipHostMalloc(&p, want, hipHostMallocDefault) != hipSuccess) {
                 (void)hipGetLastError();
+                pinned_bytes -= want;
                 p = nullptr;
                 return nullptr;
             }
@@ -133,6 +140,7 @@ struct HostStage {
     }
     void release() {
         if (p) (void)hipHostFree(p);
+        pinned_bytes -= cap;
         p = nullptr;
         cap = 0;
     }
@@ -1166,23 +1174,25 @@ lbm_status lbm_moments(lbm_handle h, double *rho, double *ux, double *uy, double
         HIP_TRY(h->ks->moments(h->dd, h->desc.storage, R.Nx, R.Ny, rho, ux, uy, T, h->stream));
         return LBM_OK;
     }
-    double *tmp = (double *)scratch_of(h, 4 * nn * sizeof(double));
-    if (!tmp) return fail(LBM_ERR_OOM, "device allocation failed");
-    double *d[4] = {tmp, tmp + nn, tmp + 2 * nn, tmp + 3 * nn};
     double *o[4] = {rho, ux, uy, T};
-    hipError_t e = h->ks->moments(h->dd, h->desc.storage, R.Nx, R.Ny, o[0] ? d[0] : nullptr,
-                                  o[1] ? d[1] : nullptr, o[2] ? d[2] : nullptr, o[3] ? d[3] : nullptr,
-                                  h->stream);
-    char *stage = h->stage.get(4 * nn * sizeof(double));
+    size_t asked = 0;
+    for (double *p : o) asked += p != nullptr;
+    double *tmp = (double *)scratch_of(h, asked * nn * sizeof(double));
+    if (!tmp) return fail(LBM_ERR_OOM, "device allocation failed");
+    double *d[4] = {};
+    for (size_t k = 0, at = 0; k < 4; ++k)
+        if (o[k]) d[k] = tmp + nn * at++;
+    hipError_t e = h->ks->moments(h->dd, h->desc.storage, R.Nx, R.Ny, d[0], d[1], d[2], d[3], h->stream);
+    char *stage = h->stage.get(asked * nn * sizeof(double));
     if (stage) {
-        if (e == hipSuccess) e = hipMemcpyAsync(stage, tmp, 4 * nn * sizeof(double), hipMemcpyDeviceToHost, h->stream);
+        if (e == hipSuccess && asked) e = hipMemcpyAsync(stage, tmp, asked * nn * sizeof(double), hipMemcpyDeviceToHost, h->stream);
     } else {
         for (int k = 0; k < 4 && e == hipSuccess; ++k)
             if (o[k]) e = hipMemcpyAsync(o[k], d[k], nn * sizeof(double), hipMemcpyDeviceToHost, h->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     for (int k = 0; stage && k < 4 && e == hipSuccess; ++k)
-        if (o[k]) std::memcpy(o[k], stage + k * nn * sizeof(double), nn * sizeof(double));
+        if (o[k]) std::memcpy(o[k], stage + (d[k] - tmp) * sizeof(double), nn * sizeof(double));
     h->mem.put(tmp);
     if (e != hipSuccess) return fail(LBM_ERR_DEVICE, std::string("lbm_moments: ") + hipGetErrorString(e));
     return LBM_OK;

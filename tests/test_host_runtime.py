@@ -192,3 +192,31 @@ for k, r in enumerate(small):
     g.step(nsteps=1)
     assert streams() == (k < 13), k
 """)
+
+
+def test_pinned_memory_is_bounded_and_moments_copy_what_is_asked(fake):
+    """The runs of a process keep at most 64 MiB of pinned memory, given back with them; the others'
+    results go straight to the caller's arrays; one field costs one plane."""
+    _play(fake, """
+runs = []
+for k in range(100):
+    r = init(run(300, 109, lattice=9))
+    r.moments()
+    runs.append(r)
+    assert F.fake_pinned() <= 64 << 20
+assert F.fake_pinned() > 60 << 20
+for r in runs:
+    r.close()
+assert F.fake_pinned() == 0
+for n in ((60, 50), (400, 300)):
+    r = init(run(*n, lattice=9))
+    a = np.zeros((2,) + n[::-1])
+    log()
+    lbm.load().lbm_moments(r.h, None, a[0].ctypes.data, None, None, 0)
+    assert [l for l in log() if "copy" in l] == ["copy %d" % (8 * n[0] * n[1])]
+    lbm.load().lbm_moments(r.h, a[0].ctypes.data, None, None, a[1].ctypes.data, 0)
+    assert sum(int(l.split()[1]) for l in log() if "copy" in l) == 16 * n[0] * n[1]
+    assert lbm.load().lbm_moments(r.h, None, None, None, None, 0) == lbm.LBM_OK
+    assert not any("copy" in l for l in log())
+    r.close()
+""")
