@@ -118,7 +118,7 @@ typedef struct {
  * fill of the ring, PML Q update) and the bulk tiles as one grid, so they run beside the
  * streaming tiles (one stream, graphs and groups allowed), and takes FP64 and FP32 runs and groups
  * with a large interior two steps per pass over it (layout 0; the last one or two steps of a call
- * singly; debug poison and event timing take single steps); split places the phase-A blocks in
+ * singly; event timing takes single steps); split places the phase-A blocks in
  * that grid: after split/8 of the bulk tiles (0..8, rounded down to a multiple of 8 blocks), or
  * -1 for the measured default (after all of the tiles when they outnumber the phase-A blocks
  * eightfold, as on large grids, else after half of them for D2Q37 in FP64, first otherwise; on small
@@ -158,7 +158,8 @@ lbm_status lbm_set_nrbc_pml_terms(lbm_handle h, unsigned flags);
 
 /* Debug flags of a run (lbm_set_debug).  LBM_DEBUG_POISON: a NaN canary.  Before the kernels of
  * every step, the buffers that the step writes in full -- the destination population buffer,
- * the new moment strips, and on characteristic sides the ring's fill and targets -- are filled
+ * the new moment strips, and on characteristic sides the ring's fill and targets, and in a two-step
+ * pass the bands that hold the level between the steps -- are filled
  * with NaN in their storage type, so a node or component that a step leaves unwritten and a
  * later kernel reads shows up as NaN in the moments (and in lbm_check).  A correct step gives
  * the same bits with and without it.  Costs one extra pass over those buffers per step; in a

@@ -640,7 +640,7 @@ LaunchSet single_set(lbm_run *h) {
     L.split = h->launch.split;
     L.split_small = split_small(L, &h, 1);
     L.stream_frame = stream_frame(&h, 1);
-    L.core_rows = h->launch.overlap == 2 && !h->prof && !L.poison ? h->core_rows : 0;
+    L.core_rows = h->launch.overlap == 2 && !h->prof ? h->core_rows : 0;
     L.nruns = 1;
     return L;
 }
@@ -1732,7 +1732,7 @@ lbm_status lbm_group_step(lbm_group_handle g, const int64_t *steps, int64_t nste
     L.split = g->launch.split;
     L.split_small = split_small(L, g->members.data(), n);
     L.stream_frame = stream_frame(g->members.data(), n);
-    L.core_rows = g->launch.overlap == 2 && !g->poison ? g->core_rows : 0;
+    L.core_rows = g->launch.overlap == 2 ? g->core_rows : 0;
     // Runs past their own count skip every kernel, so whole graphs of G batched steps serve any
     // mix of counts; the remainder is launched eagerly.
     const int G = g->launch.graph_steps, B = G > 0 ? G : EAGER_BATCH;

@@ -2175,17 +2175,25 @@ __global__ void k_advance(RunDev *const *runs, int nruns, int n, int flips) {
 // Debug canary: before the step kernels of sub-step ks, every buffer that a step writes in full
 // -- the destination populations, the new moment strips, and the ring's characteristic fill G
 // and targets P -- is filled with NaN in its own type.  A node or component that the step leaves
-// unwritten and a later kernel reads then carries NaN into the result.
+// unwritten and a later kernel reads then carries NaN into the result.  A two-step pass fills the
+// destination buffer and the bands before its first step, U, G and P before each.
+enum { POISON_ONE = 0, POISON_FIRST = 1, POISON_SECOND = 2 };
 template <class S>
-__global__ __launch_bounds__(256) void k_poison(RunDev *const *runs, Sub ks) {
+__global__ __launch_bounds__(256) void k_poison(RunDev *const *runs, Sub ks, int what) {
     using C = typename Traits<S>::C;
     CRun &R = run_of(runs, blockIdx.y);
     const int par = sub_par(R, ks);
     if (par < 0) return;
     const long long t0 = (long long)blockIdx.x * 256 + threadIdx.x, st = (long long)gridDim.x * 256;
-    GLOBAL S *f = (GLOBAL S *)R.f[par ^ 1];
     const S ns = (S)__builtin_nanf("");
-    for (long long i = t0; i < R.fsize; i += st) f[i] = ns;
+    if (what != POISON_SECOND) {
+        GLOBAL S *f = (GLOBAL S *)R.f[par ^ 1];
+        for (long long i = t0; i < R.fsize; i += st) f[i] = ns;
+    }
+    if (what == POISON_FIRST) {
+        GLOBAL S *M = (GLOBAL S *)R.M;
+        for (long long i = t0; i < R.msize; i += st) M[i] = ns;
+    }
     GLOBAL double *U = (GLOBAL double *)R.U[u_par(R, ks) ^ 1];
     for (long long i = t0; i < 4 * R.qplane; i += st) U[i] = __builtin_nan("");
     if (R.ring_n > 0 && R.G) {
@@ -2549,6 +2557,16 @@ static hipError_t launch_phase_a_bulk(const LaunchSet &L, int storage, int tx, S
     return hipGetLastError();
 }
 
+static hipError_t poison(const LaunchSet &L, int storage, Sub ks, int what, hipStream_t s) {
+    if (L.nruns <= 0) return hipSuccess;
+    LBM_DISPATCH(storage, hipLaunchKernelGGL((k_poison<S>), dim3(1024, L.nruns), dim3(256), 0, s, L.runs,
+                                             ks, what));
+    return hipGetLastError();
+}
+static hipError_t launch_poison(const LaunchSet &L, int storage, Sub ks, hipStream_t s) {
+    return poison(L, storage, ks, POISON_ONE, s);
+}
+
 // Two steps of every run in one pass over its interior: the interior's two steps, then the boundary
 // chain of the first step (characteristic fill and Q update, the frame into the bands) and of the
 // second, from the bands.  The tiles hold nearly all of a compute unit's LDS and registers, so the
@@ -2558,13 +2576,15 @@ template <class S>
 static hipError_t two_steps(const LaunchSet &L, int storage, Sub k1, hipStream_t s) {
     const Sub k2{k1.steps + 1, k1.flips};
     const dim3 tb(256), nA(L.blocks[CLS_A]);
+    hipError_t e = L.poison ? poison(L, storage, k1, POISON_FIRST, s) : hipSuccess;
     hipLaunchKernelGGL((k_core<S>), dim3(L.blocks[CLS_CORE]), dim3(CORE_X * CORE_R), 0, s, L.runs,
                        L.prefix[CLS_CORE], L.nruns, k1, L.core_rows);
-    hipError_t e = launch_target(L, storage, k1, s);
+    if (e == hipSuccess) e = launch_target(L, storage, k1, s);
     if (nA.x > 0)
         hipLaunchKernelGGL((k_phase_a<S, SRC_F>), nA, tb, 0, s, L.runs, L.prefix[CLS_A], L.nruns, k1);
     hipLaunchKernelGGL((k_frame<S, STEP_FIRST, false>), dim3(L.blocks[CLS_FRAME]), tb, 0, s, L.runs,
                        L.prefix[CLS_FRAME], L.nruns, k1);
+    if (e == hipSuccess && L.poison) e = poison(L, storage, k2, POISON_SECOND, s);
     if (e == hipSuccess) e = launch_target(L, storage, k2, s);
     if (nA.x > 0)
         hipLaunchKernelGGL((k_phase_a<S, SRC_M>), nA, tb, 0, s, L.runs, L.prefix[CLS_A], L.nruns, k2);
@@ -2582,13 +2602,6 @@ static hipError_t launch_two_steps(const LaunchSet &L, int storage, Sub k1, hipS
 
 static hipError_t launch_advance(const LaunchSet &L, int n, int flips, hipStream_t s) {
     hipLaunchKernelGGL(k_advance, dim3((L.nruns + 255) / 256), dim3(256), 0, s, L.runs, L.nruns, n, flips);
-    return hipGetLastError();
-}
-
-static hipError_t launch_poison(const LaunchSet &L, int storage, Sub ks, hipStream_t s) {
-    if (L.nruns <= 0) return hipSuccess;
-    LBM_DISPATCH(storage, hipLaunchKernelGGL((k_poison<S>), dim3(1024, L.nruns), dim3(256), 0, s, L.runs,
-                                             ks));
     return hipGetLastError();
 }
 

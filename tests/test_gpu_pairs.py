@@ -1,32 +1,16 @@
 """What two-step passes (the default schedule of large FP64 and FP32 runs) leave behind and meet beside
-the plain runs: checkpoints after an odd number of passes."""
+the plain runs: checkpoints after an odd number of passes, and the NaN canary.  That the cases do take
+pairs is asked of the host's schedule in test_host_runtime.py."""
 import struct
 
 import numpy as np
 import pytest
 
 from paper_2504_20169_amd import lbm
-from paper_2504_20169_amd import workloads as wl
 from _helpers import say
+from pair_cases import GROUP, SINGLE, make
 
 pytestmark = pytest.mark.gpu
-
-
-def _make(lattice, storage, nx, ny, bcx, bcy, W, seed, overlap=2, outlet=None, terms=0):
-    r = lbm.Run(nx, ny, 0.8, 1.0, 0.05, 0.01, 1.0, storage=storage, lattice=lattice)
-    r.set_bc(lbm.LBM_XMIN | lbm.LBM_XMAX, bcx)
-    r.set_bc(lbm.LBM_YMIN | lbm.LBM_YMAX, bcy)
-    if outlet:
-        r.set_bc(lbm.LBM_XMAX, outlet)
-    mask = (3 if bcx != "periodic" else 0) | (12 if bcy != "periodic" else 0)
-    if W and mask:
-        r.set_pml(mask, W, 0.002)
-    if terms:
-        r.set_nrbc_pml_terms(terms)
-    r.set_launch(overlap=overlap)
-    Nx, Ny = r.grid()
-    r.init(*wl.noisy_state(Nx, Ny, seed, 1.0, 0.05, 0.01, 1.0).as_tuple())
-    return r
 
 
 def _state(r):
@@ -37,12 +21,6 @@ def _same(a, b):
     return all(np.array_equal(x, y) for x, y in zip(a, b))
 
 
-def _paired(r, storage):
-    """The run alone takes its steps in pairs (by its interior and frame nodes)."""
-    interior, frame = r.node_classes()[:2]
-    return interior >= (400000 + frame if storage == "f64" else 800000 + 5 * frame)
-
-
 @pytest.mark.parametrize("steps", [5, 7, 10, 12])
 def test_checkpoint_has_one_parity(tmp_path, steps):
     """After an odd number of two-step passes (7 and 12 steps: 3 passes and a step, 5 and two) the
@@ -50,14 +28,13 @@ def test_checkpoint_has_one_parity(tmp_path, steps):
     file still names one buffer for both, the one of the step's parity, and a run that loads it
     goes on with the same bits."""
     say("checkpoint after", steps, "steps")
-    a = _make(9, "f64", 690, 671, "nrbc", "nrbc", 9, seed=8)
-    assert _paired(a, "f64")
+    a = make(9, "f64", 690, 671, "nrbc", "nrbc", 9, {}, seed=8)
     a.step(steps)
     a.save(tmp_path / "c")
     head = (tmp_path / "c").read_bytes()[:88]
     assert struct.unpack_from("<q", head, 80)[0] == steps
     assert struct.unpack_from("<i", head, 60)[0] == steps & 1
-    b = _make(9, "f64", 690, 671, "nrbc", "nrbc", 9, seed=9)
+    b = make(9, "f64", 690, 671, "nrbc", "nrbc", 9, {}, seed=9)
     b.step(4)
     b.load(tmp_path / "c")
     assert b.step_count == steps and _same(_state(a), _state(b))
@@ -66,3 +43,44 @@ def test_checkpoint_has_one_parity(tmp_path, steps):
     assert _same(_state(a), _state(b))
     a.close()
     b.close()
+
+
+def _ids(c):
+    return "q%d-%s-%dx%d-%s-%s-W%d%s" % (c[:7] + ("".join("-%s%s" % kv for kv in c[7].items()),))
+
+
+@pytest.mark.parametrize("case", SINGLE, ids=_ids)
+def test_canary_in_pairs_leaves_the_bits(case):
+    """Every buffer that a two-step pass or one of its steps writes in full, the bands of the level
+    between among them, filled with NaN before: the same bits as without, and finite."""
+    say("canary in pairs", case)
+    out = []
+    for flags in (0, lbm.LBM_DEBUG_POISON):
+        r = make(*case, seed=12)
+        r.set_debug(flags)
+        r.step(7)
+        assert r.check() == lbm.LBM_OK
+        out.append(_state(r))
+        r.close()
+    assert all(np.isfinite(x).all() for x in out[1])
+    assert _same(*out)
+
+
+def test_canary_in_a_paired_group():
+    out = []
+    for flags in (0, lbm.LBM_DEBUG_POISON):
+        g = lbm.Group()
+        runs = [make(37, "f64", *c, seed=40 + k) for k, (c, n) in enumerate(GROUP)]
+        runs[2].set_debug(flags)
+        for r in runs:
+            g.add(r)
+        say("canary in a paired group", flags)
+        g.step(steps=np.array([n for c, n in GROUP]))
+        g.synchronize()
+        assert not g.check().any()
+        out.append([_state(r) for r in runs])
+        g.close()
+        for r in runs:
+            r.close()
+    for a, b in zip(*out):
+        assert all(np.isfinite(x).all() for x in b) and _same(a, b)

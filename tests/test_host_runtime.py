@@ -18,7 +18,7 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.exist
 
 PRELUDE = """
 import ctypes, sys
-sys.path.insert(0, %r)
+sys.path[:0] = [%r, %r]
 import numpy as np
 from paper_2504_20169_amd import lbm
 F = ctypes.CDLL(%r)
@@ -52,7 +52,7 @@ def fake(tmp_path_factory):
 
 
 def _play(fake, code):
-    res = subprocess.run([sys.executable, "-c", PRELUDE % (ROOT, fake) + code + "\nprint('played')"],
+    res = subprocess.run([sys.executable, "-c", PRELUDE % (ROOT, HERE, fake) + code + "\nprint('played')"],
                          env=dict(os.environ, LD_PRELOAD=fake), capture_output=True, text=True, timeout=120)
     assert res.returncode == 0 and res.stdout.endswith("played\n"), res.stdout[-1500:] + res.stderr[-3000:]
 
@@ -219,4 +219,35 @@ for n in ((60, 50), (400, 300)):
     assert lbm.load().lbm_moments(r.h, None, None, None, None, 0) == lbm.LBM_OK
     assert not any("copy" in l for l in log())
     r.close()
+""")
+
+
+def test_the_cases_of_the_pair_tests_take_pairs(fake):
+    """Also under the NaN canary, which fills buffers before the pass and between its steps."""
+    _play(fake, """
+import pair_cases as pc
+for c in pc.SINGLE:
+    r = pc.make(*c, seed=1)
+    assert pairs(7, r) == 3, c
+    r.set_debug(lbm.LBM_DEBUG_POISON)
+    log()
+    r.step(7)
+    names = " ".join(log())
+    assert names.count("k_core") == 3 and names.count("k_poison") == 7, c
+    r.close()
+for q in (37, 17, 9):
+    g = lbm.Group()
+    runs = [pc.make(q, "f64", *c, seed=1) for c, n in pc.GROUP]
+    for r in runs:
+        g.add(r)
+    log()
+    # stops at 1, 9, 16, 17 and 40 steps: one step, 3 pairs and two, eight steps, 11 pairs and one
+    g.step(steps=np.array([n for c, n in pc.GROUP]))
+    assert sum("k_core" in l for l in log()) == 14
+    runs[0].set_debug(lbm.LBM_DEBUG_POISON)
+    assert pairs(8, g) == 3
+    for r in runs:
+        g.remove(r)
+        r.close()
+    g.close()
 """)
