@@ -1,5 +1,6 @@
 """What two-step passes (the default schedule of large FP64 and FP32 runs) leave behind and meet beside
-the plain runs: checkpoints after an odd number of passes, and the NaN canary.  That the cases do take
+the plain runs: thin grids, targets formed ahead, small members of a group, checkpoints after an odd
+number of passes, the NaN canary.  That the cases do take
 pairs is asked of the host's schedule in test_host_runtime.py."""
 import struct
 
@@ -84,3 +85,41 @@ def test_canary_in_a_paired_group():
             r.close()
     for a, b in zip(*out):
         assert all(np.isfinite(x).all() for x in b) and _same(a, b)
+
+
+@pytest.mark.parametrize("case", SINGLE, ids=_ids)
+def test_pairs_equal_single_steps_for_thin_grids_and_formed_targets(case):
+    say("pairs against single steps", case)
+    out = []
+    for overlap in (0, 2):
+        r = make(*case, seed=13, overlap=overlap)
+        for n in (6, 35):
+            r.step(n)
+        assert r.check() == lbm.LBM_OK
+        out.append(_state(r))
+        r.close()
+    assert _same(*out)
+
+
+@pytest.mark.parametrize("lattice", [37, 17, 9])
+def test_members_of_a_paired_group_equal_alone(lattice):
+    """Strips and tiles a few nodes wide beside a large run's, stops close together and far apart."""
+    alone = []
+    for k, (c, n) in enumerate(GROUP):
+        r = make(lattice, "f64", *c, seed=30 + k, overlap=0)
+        r.step(n + 23)
+        alone.append(_state(r))
+        r.close()
+    g = lbm.Group()
+    runs = [make(lattice, "f64", *c, seed=30 + k) for k, (c, n) in enumerate(GROUP)]
+    for r in runs:
+        g.add(r)
+    say("members of a paired group", lattice)
+    g.step(steps=np.array([n for c, n in GROUP]))
+    g.step(nsteps=23)
+    g.synchronize()
+    for r, a, (c, n) in zip(runs, alone, GROUP):
+        assert r.step_count == n + 23 and _same(_state(r), a), c
+    g.close()
+    for r in runs:
+        r.close()
