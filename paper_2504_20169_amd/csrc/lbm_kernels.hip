@@ -97,8 +97,11 @@ __device__ __forceinline__ long long guard(CRun &R, long long i, long long n) {
 // element `off` bytes past base, inside buffer buf of n elements
 #define LBM_AT(R, base, off, buf, n) \
     ((buf) + guard((R), ((base) - (buf)) + (long long)((off) / sizeof(*(buf))), (n)))
+// element p of buffer buf of n elements
+#define LBM_IN(R, p, buf, n) ((buf) + guard((R), (p) - (buf), (n)))
 #else
 #define LBM_GUARD(R, i, n) (i)
+#define LBM_IN(R, p, buf, n) (p)
 #define LBM_CHECK(R, i, n) ((void)0)
 #define LBM_AT(R, base, off, buf, n) at((base), (off))
 #endif
@@ -1402,8 +1405,8 @@ __device__ __forceinline__ void frame_collide(CRun &R, const K<C> &k, const C (&
         constexpr int i = decltype(ic)::value;
         const S v = cvt_out(out, k.scale, (S *)nullptr);
         if constexpr (BANDS) {
-            dnode[(Stride)i * plane] = v;
-            if (two) dnode2[(Stride)i * plane2] = v;
+            *LBM_IN(R, dnode + (Stride)i * plane, (GLOBAL S *)R.M, R.msize) = v;
+            if (two) *LBM_IN(R, dnode2 + (Stride)i * plane2, (GLOBAL S *)R.M, R.msize) = v;
         } else {
             if constexpr (STREAM) __builtin_nontemporal_store(v, dnode + (long long)i * plane);
             else dnode[(long long)i * plane] = v;
