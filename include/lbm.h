@@ -288,7 +288,8 @@ lbm_status lbm_get_launch(lbm_handle h, lbm_launch *cfg);
 /* Time every supported bulk tile shape in each schedule -- in order, on a side stream (for a
  * run that owns its stream), and fused with the phase-A blocks after 0, 2, 4, 6 or 8 eighths of
  * the tiles -- on a scratch copy of this run's geometry (the run's own state is untouched) and
- * keep the fastest; if cache_path is non-NULL the choice is read from / appended to that text
+ * keep the fastest.  A run or group that takes two steps per pass stays with the fused schedule,
+ * whose settings are timed in the single steps they shape, and takes no cached line of another; if cache_path is non-NULL the choice is read from / appended to that text
  * file, one line "Nx Ny storage lattice bulk_tx overlap split" per choice (a line without the
  * split reads as split -1).  *chosen may be NULL. */
 lbm_status lbm_autotune(lbm_handle h, int32_t steps, const char *cache_path,

@@ -1502,6 +1502,10 @@ lbm_status lbm_autotune(lbm_handle h, int32_t steps, const char *cache_path, lbm
     if (h->group) return fail(LBM_ERR_STATE, "run is in a group");
     if (steps < 1) steps = 10;
     const RunDev &R = h->hd;
+    // A run that takes pairs keeps the fused schedule, which they belong to; tile width and placement
+    // shape its single steps alone, so they are timed in those.  A line with another schedule is of
+    // single steps throughout (builds before two-step passes wrote such lines).
+    const bool paired = choose_core_rows(&h, 1) > 0;
     if (cache_path) {
         FILE *fp = std::fopen(cache_path, "r");
         if (fp) {
@@ -1509,7 +1513,7 @@ lbm_status lbm_autotune(lbm_handle h, int32_t steps, const char *cache_path, lbm
             while (std::fgets(line, sizeof line, fp)) {
                 int nx, ny, st, q, tx, ov, sp = -1;
                 if (std::sscanf(line, "%d %d %d %d %d %d %d", &nx, &ny, &st, &q, &tx, &ov, &sp) < 6) continue;
-                if (nx == R.Nx && ny == R.Ny && st == h->desc.storage && q == h->lat->q) {
+                if (nx == R.Nx && ny == R.Ny && st == h->desc.storage && q == h->lat->q && (ov == 2 || !paired)) {
                     std::fclose(fp);
                     lbm_launch c = h->launch;
                     c.bulk_tx = tx; c.bulk_ty = 256 / tx; c.overlap = ov; c.split = sp;
@@ -1540,11 +1544,13 @@ lbm_status lbm_autotune(lbm_handle h, int32_t steps, const char *cache_path, lbm
     // tile widths x schedules, and for the fused grid the phase-A placement in eighths of the tiles
     for (int ov = 0; ov < 3; ++ov) {
         if (ov == 1 && d.stream) continue;   // the side stream needs a stream the run owns
+        if (ov != 2 && paired) continue;
         for (int tx : {64, 128, 256}) {
             for (int sp : {0, 2, 4, 6, 8}) {
                 if (ov != 2 && sp != 0) continue;
                 lbm_launch c{tx, 256 / tx, 0, ov, ov == 2 ? sp : -1};
                 if (lbm_set_launch(s, &c) != LBM_OK) continue;
+                s->core_rows = 0;
                 lbm_step(s, 2);
                 (void)hipEventRecord(a, s->stream);
                 lbm_step(s, steps);
@@ -1809,6 +1815,7 @@ lbm_status lbm_group_autotune(lbm_group_handle g, int32_t steps, lbm_launch *cho
     if (!g) return fail(LBM_ERR_ARG, "NULL argument");
     if (g->members.empty()) return fail(LBM_ERR_STATE, "empty group");
     if (steps < 1) steps = 10;
+    const bool paired = set_pairs(g->members.data(), g->members.size());   // as for a run
     // one scratch run at the mean state per distinct geometry among the members
     std::vector<lbm_run *> scratch;
     std::vector<std::array<long long, 12>> keys;
@@ -1843,12 +1850,13 @@ lbm_status lbm_group_autotune(lbm_group_handle g, int32_t steps, lbm_launch *cho
         (void)hipEventCreate(&b);
         // tile widths x {in order, fused with the phase-A blocks after 0, 2, 4, 6 or 8 eighths of
         // the tiles}
-        for (int k = 0; k < 18; ++k) {
+        for (int k = paired ? 3 : 0; k < 18; ++k) {
             if (st != LBM_OK) break;
             const int tx = 64 << (k % 3), j = k / 3, ov = j == 0 ? 0 : 2, sp = j == 0 ? -1 : 2 * (j - 1);
             lbm_launch c{tx, 256 / tx, 0, ov, sp};
             if ((st = lbm_group_set_launch(sg, &c)) != LBM_OK) break;
             if ((st = lbm_group_step(sg, nullptr, 2)) != LBM_OK) break;
+            sg->core_rows = 0;
             (void)hipEventRecord(a, g->stream);
             if ((st = lbm_group_step(sg, nullptr, steps)) != LBM_OK) break;
             (void)hipEventRecord(b, g->stream);

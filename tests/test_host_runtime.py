@@ -251,3 +251,33 @@ for q in (37, 17, 9):
         r.close()
     g.close()
 """)
+
+
+def test_autotune_keeps_pairs(fake, tmp_path):
+    """A run or group that pairs is tuned within the fused schedule, timed in single steps, and a cached
+    line of another schedule does not switch its pairs off; one that does not pair takes any line."""
+    cache = str(tmp_path / "tune")
+    with open(cache, "w") as f:
+        f.write("700 700 0 9 128 0 -1\n200 200 0 9 128 0 -1\n")
+    _play(fake, """
+cache = %r
+r = init(run(700, 700, lattice=9))
+log()
+assert r.autotune(steps=8, cache_path=cache)["overlap"] == 2
+assert not any("k_core" in l for l in log())
+assert pairs(of=r) == 3
+lines = open(cache).read().splitlines()
+assert len(lines) == 3 and lines[2].split()[5] == "2"
+again = init(run(700, 700, lattice=9))
+log()
+assert again.autotune(steps=8, cache_path=cache) == r.get_launch()
+assert len(open(cache).read().splitlines()) == 3
+small = init(run(200, 200, lattice=9))
+assert small.autotune(steps=8, cache_path=cache)["overlap"] == 0
+g = lbm.Group()
+g.add(r)
+log()
+assert g.autotune(steps=8)["overlap"] == 2
+assert not any("k_core" in l for l in log())
+assert pairs(of=g) == 3
+""" % cache)
