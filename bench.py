@@ -306,9 +306,10 @@ KERNEL_SRC = [os.path.join(ROOT, "paper_2504_20169_amd", "csrc", n)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_f64_1088sq_nrbc_pmc.txt")
 # the FP64 D2Q37 kernels whose HBM traffic the counter summary records, by short name
 TRACKED = {
-    "grid": "void lbm::k37::k_phase_a_bulk<double, 64>(lbm::RunDev* const*, int const*, int, int const*, int, int, int, int)",
-    "frame": "void lbm::k37::k_frame<double>(lbm::RunDev* const*, int const*, int, int)",
-    "bulk": "void lbm::k37::k_bulk<double, 64>(lbm::RunDev* const*, int const*, int, int)",
+    "grid": "void lbm::k37::k_phase_a_bulk<double, 64>(lbm::RunDev* const*, int const*, int, int const*, int, int, int, lbm::Sub)",
+    "frame": "void lbm::k37::k_frame<double, 0, true>(lbm::RunDev* const*, int const*, int, lbm::Sub)",
+    "bulk": "void lbm::k37::k_bulk<double, 64>(lbm::RunDev* const*, int const*, int, lbm::Sub)",
+    "pass": "void lbm::k37::k_core<double>(lbm::RunDev* const*, int const*, int, lbm::Sub, int)",
 }
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
@@ -540,7 +541,7 @@ def pmc_means_all(path):
 
 
 def recorded_traffic(short):
-    """HBM bytes per launch of a tracked kernel ("grid", "frame" or "bulk") from the committed
+    """HBM bytes per launch of a tracked kernel (a key of TRACKED) from the committed
     counter summary, or None when it is missing or was taken from another version of the
     kernels."""
     try:
@@ -583,10 +584,16 @@ def host_cpu():
 
 
 def roofline_entry(R, args, storage, copy_gbs):
-    """The roofline object of the bench line: the dominant kernel of the timed steps (the grid
-    of phase A and the bulk tiles in the fused schedule, else the bulk kernel), with the frame
-    kernel and the whole step beside it."""
+    """The roofline object of the bench line: the dominant kernel of single steps (the grid of phase A
+    and the bulk tiles in the fused schedule, else the bulk kernel), with the frame kernel and the
+    whole step beside it.  A run that takes two steps per pass spends its timed steps, but for the last
+    one or two of a call, in the two-step kernels, which carry no events: of those the object has the
+    interior's pass, its algorithmic bytes and its counted traffic."""
     fused = args.overlap == 2
+    nb, nf = R["bulk_nodes"], R["frame_nodes"]
+    # the library's line (two_steps_pay), for the default layout
+    paired = fused and args.layout == 0 and \
+        {"f64": nb >= 400000 + nf, "f32": nb >= 800000 + 5 * nf}.get(storage, False)
     tracked = storage == "f64" and args.L == 1024 and args.W == 32 and args.bc == "nrbc" and \
         args.layout == 0 and args.bulk_tx == 64 and fused
     gbs, fgbs = R.get("grid_gbs"), R.get("frame_gbs")
@@ -610,6 +617,11 @@ def roofline_entry(R, args, storage, copy_gbs):
             "bytes_per_launch": R["frame_bytes_per_launch"],
             "avg_launch_ms": round(R["frame_kernel_ms"], 5),
         },
+        "two_step_pass": {
+            "kernel": "k_core (two steps of the interior per launch), most of the timed steps; no events",
+            "traffic": recorded_traffic("pass") if tracked else None,
+            "bytes_per_launch": bytes_per_node(storage, 37) * nb,
+        } if paired else None,
         "whole_step": {"achieved": round(R["gbs_step"], 1), "frac": round(R["frac_step"], 4),
                        "ms_per_step": round(R["ms_per_step"], 5)},
         "device_copy_gbs": round(copy_gbs, 1) if copy_gbs else None,

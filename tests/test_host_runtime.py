@@ -281,3 +281,21 @@ assert g.autotune(steps=8)["overlap"] == 2
 assert not any("k_core" in l for l in log())
 assert pairs(of=g) == 3
 """ % cache)
+
+
+@pytest.mark.skipif(shutil.which("c++filt") is None, reason="c++filt not found")
+def test_tracked_kernels_of_the_benchmark_exist(fake):
+    """The counter summary of the benchmark finds its kernels by their demangled names."""
+    _play(fake, """
+import subprocess
+import bench
+seen = set()
+r = init(run(1024, 1024, W=32, bc="nrbc"))
+for overlap in (2, 0):
+    r.set_launch(overlap=overlap)
+    log()
+    r.step(6)
+    seen |= set(l[4:] for l in log() if l.startswith("run "))
+names = subprocess.run(["c++filt"], input="\\n".join(seen), capture_output=True, text=True, check=True).stdout.split("\\n")
+assert set(bench.TRACKED.values()) <= set(names), names
+""")
