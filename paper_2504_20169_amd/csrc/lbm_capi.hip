@@ -266,7 +266,11 @@ namespace {
 // 66.0, 768^2 ZG 101.3 / 89.5, 1024^2 NRBC 172.4 / 151.7, 4096^2 2214 / 1627; D2Q17 768^2 51.8 /
 // 50.5, D2Q9 768^2 30.8 / 28.1 (512^2 35.0 / 36.9 and 23.0 / 22.3).  FP32, whose tiles are bound by
 // arithmetic: 1024^2 without a layer 72.2 / 63.7, with 32 cells 96.2 / 100.2, 2048^2 with 32 cells
-// 285 / 236.  FP16 never: half the bytes to save, and 48-column stores in place of whole lines
+// 285 / 236; by the same line D2Q17 1024^2 ZG with 8 cells 39.0 / 37.3, 1600^2 NRBC with 32 92.9 / 78.5,
+// below it 1024^2 periodic by NRBC with 20 39.4 / 42.4; D2Q9 24.6 / 22.9 and 45.0 / 35.8 (1600^2
+// without a layer).  Tall grids with characteristic ends gain least: D2Q37 FP32 400 x 3000 with 20
+// cells 89.5 / 97.8 against split boundary launches, 98.0 without those.  Down to the shortest side:
+// FP64 4200 x 104 (98 rows inside) 58.9 / 47.0, 110 x 4000 97.9 / 85.4.  FP16 never: half the bytes to save, and 48-column stores in place of whole lines
 // (1024^2 57.6 / 113.9).
 constexpr int TWO_STEP_MIN_SIDE = 96;
 bool two_steps_pay(int storage, long long interior, long long frame) {

@@ -1506,7 +1506,8 @@ template <int D> __device__ __forceinline__ int core_slot(int w, int odd) {
 // Rows of populations through a buffer resource: population i of a grid row sits i population rows
 // past the row's start (the row layout), so an access is one scalar multiple of the population
 // row's size, one per-lane offset and an immediate, and no 64-bit address per population: with
-// those the FP32 tile spilled 81 scalar registers, which hold the equilibrium's constants now.
+// those the FP32 tile spilled 81 scalar registers, which hold the equilibrium's constants now.  (What
+// still spills: D2Q37 FP64 43 scalar registers, FP32 21 and 6 vector registers, 28 bytes a lane.)
 // The resource ends with the rows it covers.
 template <class S> struct Rows {
     __amdgpu_buffer_rsrc_t r;
