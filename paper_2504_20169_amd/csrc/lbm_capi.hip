@@ -216,7 +216,7 @@ struct lbm_run {
     DeviceMem mem;
     GraphCache graphs;
     int prof = 0;                     // 0 off, 1 classes in order, 2 bulk kernel in the normal schedule,
-                                      // 3 as 2 on the first step of each batch only
+                                      // 3 as 2 on every fourth step only
     struct Ev { hipEvent_t a, b; int cls; };
     std::vector<Ev> pending;
     std::vector<hipEvent_t> pool;
@@ -1101,6 +1101,7 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
     }
     lbm_status ps = upload_prefix(h);
     if (ps != LBM_OK) return ps;
+    (void)h->stage.get(sizeof(int));   // lbm_check's
     h->inited = true;
     h->steps = 0;
     return LBM_OK;
@@ -1330,7 +1331,7 @@ lbm_status lbm_check(lbm_handle h) {
     if (!h->inited) return fail(LBM_ERR_STATE, "not initialised");
     int *flag = h->dflag;
     int hf = 0;
-    int *stage = (int *)h->stage.get(sizeof(int)), *hflag = stage ? stage : &hf;
+    int *stage = (int *)h->stage.p, *hflag = stage ? stage : &hf;   // (allocates nothing)
     hipError_t e = hipMemsetAsync(flag, 0, sizeof(int), h->stream);
     if (e == hipSuccess) e = h->ks->check(h->dd, h->desc.storage, h->hd.Nx, h->hd.Ny, flag, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);

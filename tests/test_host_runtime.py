@@ -299,3 +299,19 @@ for overlap in (2, 0):
 names = subprocess.run(["c++filt"], input="\\n".join(seen), capture_output=True, text=True, check=True).stdout.split("\\n")
 assert set(bench.TRACKED.values()) <= set(names), names
 """)
+
+
+def test_check_allocates_nothing(fake):
+    """The health check, also of lbm_step's check interval, may run while another stream of the process is
+    being captured: its flag's pinned memory is taken when the run is initialised."""
+    _play(fake, """
+r = init(run(64, 64, lattice=9))
+before = F.fake_used(), F.fake_pinned()
+assert before[1] > 0
+assert r.check() == lbm.LBM_OK
+r.set_check_interval(4)
+r.step(9)
+assert (F.fake_used(), F.fake_pinned()) == before
+r.close()
+assert F.fake_pinned() == 0
+""")
