@@ -204,7 +204,8 @@ struct lbm_run {
     int *dprefix = nullptr;   // [NCLS][2] prefix arrays of the single-run launch set
     int nblocks[NCLS] = {};
     int core_rows = 0;        // rows of a two-step tile; 0: single steps only
-    bool no_bands = false;    // its two-step bands made room for another buffer: none any more
+    bool own_bands = false;   // its two-step bands are its own, not its group's
+    bool no_bands = false;    // they made room for another buffer: none any more
     const LatticeInfo *lat = &LATTICE_D2Q37;   // velocity stencil
     const KernelSet *ks = &k37::kernels;       // its kernels
     double fbar[NQ_MAX];
@@ -242,6 +243,9 @@ struct lbm_group {
     lbm_launch launch{64, 4, 32, 2, -1};
     GraphCache graphs;                // batched steps of the current membership
     int core_rows = 0;                // rows of a two-step tile; 0: single steps only
+    void *bands = nullptr;            // two-step bands of the members that have none of their own
+    size_t bands_cap = 0;
+    bool no_bands = false;            // they made room for another buffer: none for this membership
     RunDev **druns = nullptr;
     int *dprefix = nullptr;
     long long *dlimits = nullptr;
@@ -577,38 +581,83 @@ lbm_status upload_prefix(lbm_run *h) {
     return LBM_OK;
 }
 
-// The two-step bands of a run: taken once a set that it is in takes its steps in pairs, after all
-// else, and given back when it is in none or when another buffer finds no memory.  Without them the
-// run takes single steps, whose bits are the same.  The run's stream is idle.
+// The two-step bands.  A run that pairs by itself takes its own, after all else; a group that pairs has
+// one block for its other members while they are in it.  They make room for a buffer that finds no
+// memory; without them a set takes single steps, whose bits are the same.  The set's stream is idle.
 lbm_status set_bands(lbm_run *h, void *M) {
     h->hd.M = M;
     HIP_TRY(hipMemcpyAsync((char *)h->dd + offsetof(RunDev, M), &h->hd.M, sizeof(void *), hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
     return LBM_OK;
 }
 lbm_status take_bands(lbm_run *h) {
-    if (h->hd.M) return LBM_OK;
     void *M = h->mem.get((size_t)h->hd.msize * elem_size(h->desc.storage));
     if (!M) return LBM_OK;
     if (h->mem.overlapping()) return fail(LBM_ERR_ARG, "device buffers overlap: the allocator returned aliasing memory");
+    h->own_bands = true;
     return set_bands(h, M);
 }
 lbm_status drop_bands(lbm_run *h) {
     void *M = h->hd.M;
-    if (!M) return LBM_OK;
     lbm_status st = set_bands(h, nullptr);
-    if (st == LBM_OK) h->mem.put(M);
-    return st;
+    if (st != LBM_OK) return st;
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    if (h->own_bands) h->mem.put(M);
+    h->own_bands = false;
+    return LBM_OK;
+}
+bool in_group_bands(const lbm_run *h) { return h->hd.M && !h->own_bands; }
+
+lbm_status drop_group_bands(lbm_group *g) {
+    for (lbm_run *h : g->members)
+        if (in_group_bands(h)) {
+            lbm_status st = drop_bands(h);
+            if (st != LBM_OK) return st;
+        }
+    g->mem.put(g->bands);
+    g->bands = nullptr;
+    g->bands_cap = 0;
+    return LBM_OK;
+}
+lbm_status take_group_bands(lbm_group *g) {
+    size_t need = 0;
+    const auto bytes = [](const lbm_run *h) {
+        return (size_t)round_up(h->hd.msize * (long long)elem_size(h->desc.storage), 256);
+    };
+    for (lbm_run *h : g->members) need += h->own_bands ? 0 : bytes(h);
+    if (need == 0 || need > g->bands_cap) {
+        lbm_status st = drop_group_bands(g);
+        if (st != LBM_OK || need == 0) return st;
+        g->bands = g->mem.get(need);
+        if (!g->bands) return LBM_OK;
+        g->bands_cap = need;
+        if (g->mem.overlapping()) return fail(LBM_ERR_ARG, "device buffers overlap: the allocator returned aliasing memory");
+    }
+    char *at = (char *)g->bands;
+    for (lbm_run *h : g->members) {
+        if (h->own_bands) continue;
+        if (h->hd.M != at) {
+            lbm_status st = set_bands(h, at);
+            if (st != LBM_OK) return st;
+        }
+        at += bytes(h);
+    }
+    HIP_TRY(hipStreamSynchronize(g->stream));
+    return LBM_OK;
 }
 
-// Device scratch of a call; if there is none, the run's bands make room for it.
+// Device scratch of a call; if there is none, the run's bands, or its group's, make room for it.
 void *scratch_of(lbm_run *h, size_t bytes) {
     void *p = h->mem.get(bytes);
     if (p || !h->hd.M || hipStreamSynchronize(h->stream) != hipSuccess) return p;
-    h->no_bands = true;
-    h->graphs.drop();
     if (h->group) h->group->dirty = true;
-    if (drop_bands(h) != LBM_OK || upload_prefix(h) != LBM_OK) return nullptr;
+    if (in_group_bands(h)) {
+        h->group->no_bands = true;
+        if (drop_group_bands(h->group) != LBM_OK) return nullptr;
+    } else {
+        h->no_bands = true;
+        h->graphs.drop();
+        if (drop_bands(h) != LBM_OK || upload_prefix(h) != LBM_OK) return nullptr;
+    }
     return h->mem.get(bytes);
 }
 
@@ -1623,6 +1672,7 @@ lbm_status lbm_group_add(lbm_group_handle g, lbm_handle h) {
     g->storage = h->desc.storage;
     g->ks = h->ks;
     g->members.push_back(h);
+    g->no_bands = false;
     h->group = g;
     h->stream = g->stream;
     g->dirty = true;
@@ -1634,10 +1684,13 @@ lbm_status lbm_group_remove(lbm_group_handle g, lbm_handle h) {
     auto it = std::find(g->members.begin(), g->members.end(), h);
     if (it == g->members.end()) return fail(LBM_ERR_ARG, "run is not in this group");
     HIP_TRY(hipStreamSynchronize(g->stream));
-    if (!pairs_alone(h->hd, h->desc.storage)) {
+    if (in_group_bands(h)) {
         lbm_status st = drop_bands(h);
         if (st != LBM_OK) return st;
+        if (std::none_of(g->members.begin(), g->members.end(), in_group_bands) && (st = drop_group_bands(g)) != LBM_OK)
+            return st;
     }
+    g->no_bands = false;
     g->members.erase(it);
     h->group = nullptr;
     h->stream = h->own_stream ? h->own_stream : (hipStream_t)h->desc.stream;
@@ -1676,20 +1729,10 @@ static lbm_status group_rebuild(lbm_group *g) {
     std::vector<RunDev *> ptrs(n);
     std::vector<int> pre(NCLS * (g->cap + 1), 0);
     int tot[NCLS] = {};
-    // bands for a group that takes pairs; members that have them for no use go without
-    if (set_pairs(g->members.data(), n))
-        for (lbm_run *h : g->members) {
-            lbm_status st = take_bands(h);
-            if (st != LBM_OK) return st;
-            if (!h->hd.M) break;
-        }
+    const bool paired = !g->no_bands && set_pairs(g->members.data(), n);
+    lbm_status bs = paired ? take_group_bands(g) : drop_group_bands(g);
+    if (bs != LBM_OK) return bs;
     g->core_rows = choose_core_rows(g->members.data(), n);
-    if (g->core_rows == 0)
-        for (lbm_run *h : g->members)
-            if (!pairs_alone(h->hd, h->desc.storage)) {
-                lbm_status st = drop_bands(h);
-                if (st != LBM_OK) return st;
-            }
     for (size_t k = 0; k < n; ++k) {
         lbm_run *h = g->members[k];
         ptrs[k] = h->dd;
@@ -1888,7 +1931,7 @@ void lbm_group_destroy(lbm_group_handle g) {
     if (!g) return;
     (void)hipStreamSynchronize(g->stream);
     for (lbm_run *h : g->members) {
-        if (!pairs_alone(h->hd, h->desc.storage)) (void)drop_bands(h);
+        if (in_group_bands(h)) (void)drop_bands(h);
         h->group = nullptr;
         h->stream = h->own_stream ? h->own_stream : (hipStream_t)h->desc.stream;
     }

@@ -17,7 +17,7 @@ struct Graph { std::vector<std::string> nodes; };
 struct Exec { std::vector<std::string> nodes; Stream *on = nullptr; };
 
 std::map<void *, size_t> dev, pinned;
-size_t dev_used = 0, pinned_used = 0, dev_limit = SIZE_MAX, refuse_at_least = SIZE_MAX, refuse_below = SIZE_MAX;
+size_t dev_used = 0, dev_mallocs = 0, pinned_used = 0, dev_limit = SIZE_MAX, refuse_at_least = SIZE_MAX, refuse_below = SIZE_MAX;
 std::map<const void *, std::string> kernels;
 std::string text;
 Stream *capturing = nullptr;
@@ -53,12 +53,14 @@ extern "C" {
 void fake_limit(size_t bytes) { dev_limit = bytes; }
 void fake_refuse(size_t from, size_t below) { refuse_at_least = from; refuse_below = below; }
 size_t fake_used(void) { return dev_used; }
+size_t fake_mallocs(void) { return dev_mallocs; }
 size_t fake_pinned(void) { return pinned_used; }
 const char *fake_log(void) { static std::string out; out.swap(text); text.clear(); return out.c_str(); }
 
 int hipMalloc(void **p, size_t n) {
     if (dev_used + n > dev_limit || (n >= refuse_at_least && n < refuse_below)) return fail(2);
     *p = take(dev, dev_used, n);
+    ++dev_mallocs;
     return 0;
 }
 int hipFree(void *p) { give(dev, dev_used, p); return 0; }
@@ -70,7 +72,10 @@ int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *) {
     std::memcpy(d, s, n);
     return 0;
 }
-int hipMemsetAsync(void *, int, size_t, void *) { return 0; }   // (no kernel reads it)
+int hipMemsetAsync(void *p, int v, size_t n, void *) {   // (no kernel reads a field)
+    if (n <= 4096) std::memset(p, v, n);
+    return 0;
+}
 int hipGetLastError(void) { int e = last_error; last_error = 0; return e; }
 const char *hipGetErrorString(int e) { return e == 2 ? "out of memory" : e ? "error" : "no error"; }
 int hipGetDevice(int *d) { *d = 0; return 0; }

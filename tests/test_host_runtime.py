@@ -315,3 +315,24 @@ assert (F.fake_used(), F.fake_pinned()) == before
 r.close()
 assert F.fake_pinned() == 0
 """)
+
+
+def test_bands_of_a_group_are_one_allocation(fake):
+    """The first step of a new group that pairs allocates once for all its members' bands."""
+    _play(fake, """
+big = init(run(720, 700, lattice=9))
+small = [init(run(120, 110, lattice=9)) for _ in range(5)]
+g = lbm.Group()
+for r in [big] + small:
+    g.add(r)
+F.fake_mallocs.restype = ctypes.c_size_t
+n = F.fake_mallocs()
+assert pairs(of=g) == 3
+assert F.fake_mallocs() == n + 5          # the group's four arrays and the bands
+F.fake_limit(F.fake_used())               # nothing left: a result of a member takes the block
+small[2].moments()
+assert pairs(of=g) == 0
+F.fake_limit(1 << 62)
+g.remove(small[0])
+assert pairs(of=g) == 3
+""")
