@@ -146,6 +146,41 @@ struct HostStage {
     }
 };
 
+// lbm_check's flags in pinned host memory: one page of the process, held until it ends, a flag to each
+// run from its init to its end (a pinned allocation takes 150 us, and lbm_check makes none, so that
+// it may run while another stream of the process is being captured).
+struct CheckFlags {
+    static constexpr size_t BYTES = 4096;
+    std::mutex mu;
+    int *page = nullptr;
+    std::vector<int *> unused;
+    // a flag, or NULL: the caller then copies to pageable memory
+    int *take() {
+        std::lock_guard<std::mutex> lock(mu);
+        if (!page) {
+            if (hipHostMalloc((void **)&page, BYTES, hipHostMallocPortable) != hipSuccess) {
+                (void)hipGetLastError();
+                page = nullptr;
+                return nullptr;
+            }
+            for (size_t k = BYTES / sizeof(int); k-- > 0;) unused.push_back(page + k);
+        }
+        if (unused.empty()) return nullptr;
+        int *p = unused.back();
+        unused.pop_back();
+        return p;
+    }
+    void give(int *p) {
+        if (!p) return;
+        std::lock_guard<std::mutex> lock(mu);
+        unused.push_back(p);
+    }
+};
+CheckFlags &check_flags() {
+    static CheckFlags *f = new CheckFlags;   // outlives every run
+    return *f;
+}
+
 int tx_index(int tx) { return tx == 64 ? 0 : tx == 128 ? 1 : 2; }
 
 // Side stream and events of the per-step fork/join: the bulk kernel runs on the main stream while
@@ -225,6 +260,7 @@ struct lbm_run {
     int64_t prof_n[3] = {0, 0, 0};
     lbm_group *group = nullptr;
     int *dflag = nullptr;             // lbm_check's flag, allocated with the run
+    int *hflag = nullptr;             // and its pinned copy
     HostStage stage;
     unsigned debug = 0;               // lbm_set_debug flags
     int64_t check_every = 0;          // lbm_set_check_interval: steps between checks in lbm_step
@@ -1150,7 +1186,7 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
     }
     lbm_status ps = upload_prefix(h);
     if (ps != LBM_OK) return ps;
-    (void)h->stage.get(sizeof(int));   // lbm_check's
+    h->hflag = check_flags().take();
     h->inited = true;
     h->steps = 0;
     return LBM_OK;
@@ -1380,7 +1416,7 @@ lbm_status lbm_check(lbm_handle h) {
     if (!h->inited) return fail(LBM_ERR_STATE, "not initialised");
     int *flag = h->dflag;
     int hf = 0;
-    int *stage = (int *)h->stage.p, *hflag = stage ? stage : &hf;   // (allocates nothing)
+    int *hflag = h->hflag ? h->hflag : &hf;
     hipError_t e = hipMemsetAsync(flag, 0, sizeof(int), h->stream);
     if (e == hipSuccess) e = h->ks->check(h->dd, h->desc.storage, h->hd.Nx, h->hd.Ny, flag, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
@@ -1446,6 +1482,7 @@ void lbm_destroy(lbm_handle h) {
     for (auto e : h->pool) (void)hipEventDestroy(e);
     h->mem.release_all();
     h->stage.release();
+    check_flags().give(h->hflag);
     h->ss.destroy();
     if (h->own_stream) (void)hipStreamDestroy(h->own_stream);
     delete h;
