@@ -74,6 +74,11 @@ r.init(1.0, 0.0, 0.0, 1.0)
 assert r.footprint() < peak and F.fake_used() < with_bands
 assert pairs(of=r) == 0
 r.close()
+for spare in (0, 1000, 1 << 24):     # the bands fit until the staging is asked for, or beside it
+    F.fake_limit(with_bands + spare)
+    r = init(run(6500, 103, W=4, bc="zg"))
+    assert F.fake_used() == with_bands and pairs(of=r) == 3
+    r.close()
 F.fake_limit(1 << 62)
 b = init(run(1024, 1024, W=32, bc="nrbc", storage="f32"))     # no pairs by itself
 assert F.fake_used() <= b.footprint() - 4 * 8 * 1088 * 1088 + 8192
