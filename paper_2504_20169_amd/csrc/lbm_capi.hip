@@ -709,12 +709,11 @@ bool split_small(const LaunchSet &L, lbm_run *const *runs, size_t n) {
     return L.blocks[CLS_SPLIT] <= split_most(runs[0]->lat->q, (int)elem_size(runs[0]->desc.storage), ring, interior);
 }
 
-// Whether the frame kernel streams its stores (see frame_stream_most).
 bool stream_frame(lbm_run *const *runs, size_t n) {
     const size_t es = elem_size(runs[0]->desc.storage);
     size_t bytes = 0;
     for (size_t k = 0; k < n; ++k) bytes += 2 * es * runs[k]->lat->q * runs[k]->hd.Nx * runs[k]->hd.Ny;
-    return es == 8 || bytes < frame_stream_most((int)es);
+    return frame_streams((int)es, bytes);
 }
 
 LaunchSet single_set(lbm_run *h) {

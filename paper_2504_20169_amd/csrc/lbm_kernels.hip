@@ -1399,8 +1399,8 @@ __device__ __forceinline__ void frame_collide(CRun &R, const K<C> &k, const C (&
                                               GLOBAL double *__restrict__ Un) {
     // FP64 streams to a buffer, which is next read a whole step later (frame launch, streaming /
     // ordinary stores: 1088^2 40.0 / 39.5 us, 4224^2 295 / 298); FP32 and FP16 do so in small sets
-    // (1088^2 FP32 25.1 / 22.6, FP16 20.8 / 18.5, 4224^2 FP32 181 / 161; frame_stream_most has the
-    // small).  The bands are read by the next kernel.
+    // (1088^2 FP32 25.1 / 22.6, FP16 20.8 / 18.5, 4224^2 FP32 181 / 161; frame_streams has the
+    // line).  The bands are read by the next kernel.
     auto put = [&](auto ic, C out) {
         constexpr int i = decltype(ic)::value;
         const S v = cvt_out(out, k.scale, (S *)nullptr);

@@ -180,12 +180,13 @@ for nx, ny, bx, by, W, storage, lattice, split in (
 
 
 def test_frame_stores_stream_in_small_sets(fake):
-    """The whole-node frame kernel streams FP64 always, FP32 and FP16 while the population buffers of
-    the run or group stay small."""
+    """The whole-node frame kernel streams FP64 always, FP32 and FP16 while the populations of the run
+    or group are few, FP16 again where they are many."""
     _play(fake, """
 streams = lambda: "ELb1E" in [l for l in log() if "k_frame" in l][-1]
 for nx, ny, storage, lattice, want in ((65, 1311, "f32", 9, True), (700, 700, "f32", 9, True), (800, 800, "f32", 9, False), (900, 900, "f64", 9, True),
-                                       (500, 500, "f16", 9, True), (1100, 1100, "f16", 9, False)):
+                                       (500, 500, "f16", 9, True), (1100, 1100, "f16", 9, False), (1780, 1780, "f16", 37, False),
+                                       (1830, 1830, "f16", 37, True), (2000, 300, "f32", 37, False)):
     r = init(run(nx, ny, W=12, bc="nrbc", storage=storage, lattice=lattice))
     r.step(1)
     assert streams() == want, (nx, ny, storage)
