@@ -1115,14 +1115,26 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
     }
     R.Q = R.has_q ? h->mem.get((size_t)h->lat->q * R.qplane * cs) : nullptr;
     R.G = R.ring_n > 0 ? h->mem.get((size_t)h->lat->q * R.rplane * cs) : nullptr;
-    R.M = nullptr;
+    // The bands here, beside what they are read with (the second step's frame kernel at 1088^2 FP64 takes
+    // 38.7 us, 40.7 with the bands past the staging of the fields); they make room for what follows.
+    const bool paired = pairs_alone(R, storage);
+    R.M = paired ? h->mem.get((size_t)R.msize * es) : nullptr;
+    h->own_bands = R.M != nullptr;
+    const auto need = [&](size_t bytes) {
+        void *p = h->mem.get(bytes);
+        if (p || !R.M) return p;
+        h->mem.put(R.M);
+        R.M = nullptr;
+        h->own_bands = false;
+        return h->mem.get(bytes);
+    };
     const bool need_p = R.tgt_pre && R.ring_n > 0;
-    R.P = need_p ? (double *)h->mem.get(4 * (size_t)R.rplane * sizeof(double)) : nullptr;
-    h->dd = (RunDev *)h->mem.get(sizeof(RunDev));
-    h->dptr = (RunDev **)h->mem.get(sizeof(RunDev *));
-    h->dprefix = (int *)h->mem.get(2 * NCLS * sizeof(int));
-    h->fbar_d = (double *)h->mem.get(h->lat->q * sizeof(double));
-    h->dflag = (int *)h->mem.get(sizeof(int));
+    R.P = need_p ? (double *)need(4 * (size_t)R.rplane * sizeof(double)) : nullptr;
+    h->dd = (RunDev *)need(sizeof(RunDev));
+    h->dptr = (RunDev **)need(sizeof(RunDev *));
+    h->dprefix = (int *)need(2 * NCLS * sizeof(int));
+    h->fbar_d = (double *)need(h->lat->q * sizeof(double));
+    h->dflag = (int *)need(sizeof(int));
     if ((R.has_q && !R.Q) || (R.ring_n > 0 && !R.G) || (need_p && !R.P) || !h->dd || !h->dptr || !h->dprefix ||
         !h->fbar_d || !h->dflag) {
         h->mem.release_all();
@@ -1146,13 +1158,6 @@ lbm_status lbm_init_fields(lbm_handle h, const double *rho, const double *ux, co
     HIP_TRY(hipMemcpyAsync(h->dd, &h->hd, sizeof(RunDev), hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(h->dptr, &h->dd, sizeof(RunDev *), hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(h->fbar_d, h->fbar, h->lat->q * sizeof(double), hipMemcpyHostToDevice, h->stream));
-    // The bands before the staging of the fields: beside the run's other buffers the second step's frame
-    // kernel reads them in 38.7 us, past the staging in 40.7 (1088^2 FP64).  They make room for it.
-    const bool paired = pairs_alone(R, storage);
-    if (paired && (st = take_bands(h)) != LBM_OK) {
-        h->mem.release_all();
-        return st;
-    }
     // fields to the device
     double *dfield = (double *)h->mem.get(4 * nn * sizeof(double));
     if (!dfield && h->hd.M && drop_bands(h) == LBM_OK) dfield = (double *)h->mem.get(4 * nn * sizeof(double));
