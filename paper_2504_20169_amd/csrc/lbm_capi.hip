@@ -712,8 +712,13 @@ bool split_small(const LaunchSet &L, lbm_run *const *runs, size_t n) {
 bool stream_frame(lbm_run *const *runs, size_t n) {
     const size_t es = elem_size(runs[0]->desc.storage);
     size_t bytes = 0;
-    for (size_t k = 0; k < n; ++k) bytes += 2 * es * runs[k]->lat->q * runs[k]->hd.Nx * runs[k]->hd.Ny;
-    return frame_streams((int)es, bytes);
+    long long columns = 0, rows = 0;
+    for (size_t k = 0; k < n; ++k) {
+        bytes += 2 * es * runs[k]->lat->q * runs[k]->hd.Nx * runs[k]->hd.Ny;
+        columns += runs[k]->hd.Nx;
+        rows += runs[k]->hd.Ny;
+    }
+    return frame_streams((int)es, bytes, rows > 2 * columns);
 }
 
 LaunchSet single_set(lbm_run *h) {

@@ -157,17 +157,18 @@ constexpr int split_most(int q, int elem, bool ring, long long interior) {
 static_assert(SPLIT_BLOCK == RING_BLOCK, "the split launch has the ring's blocks");
 
 // Whether the frame kernel of single steps streams its stores, for a set whose populations have this
-// many bytes (two levels, without padding).  FP64 does.  FP32 and FP16 rows of the side strips start
+// many bytes (two levels, without padding); tall: more than twice as many rows as columns.  FP64 does.  FP32 and FP16 rows of the side strips start
 // and end inside 64-byte pieces, which the cache joins with their neighbours' when they are ordinary
 // stores; but those push out what the next step reads, while the state is about what the L2s hold (32
 // MB), and in FP16 cost the next grid more than they save once it is past the Infinity Cache.  us per
 // step, streaming and ordinary: D2Q9 FP32 89 x 1335 (9 MB) 14.9, 15.6, D2Q37 FP32 591 x 145 (25 MB)
 // 21.8, 22.7 and 370^2 (41 MB) 27.7, 28.6, D2Q17 FP32 89 x 1335 (16 MB) 19.9, 20.6; D2Q37 FP32 130 x
-// 1266 (49 MB) 41.3, 36.8, 1032^2 (315 MB) 87.1, 83.6.  FP16 D2Q37 470^2 (33 MB) 37.2, 37.7, D2Q9 1032^2
+// 1266 (49 MB) 41.3, 36.8, 576^2 ZG (98 MB) 38.0, 39.7, 1032^2 (315 MB) 87.1, 83.6, D2Q17 1032^2 (145
+// MB) 43.9, 41.9, 280 x 3580 (136 MB) 68.8, 61.5, D2Q9 820^2 (48 MB) 22.8, 23.5.  FP16 D2Q37 470^2 (33 MB) 37.2, 37.7, D2Q9 1032^2
 // (38 MB) 22.4, 19.2, D2Q17 1764^2 (212 MB) 66.6, 58.3, D2Q37 1764^2 (461 MB) 159.2, 152.9; 2064^2 ZG
 // (630 MB) 184.7, 191.0, D2Q17 4112^2 ZG (1150 MB) 248.4, 255.3, with a ring even (1177 MB 284.4, 284.4).
-constexpr bool frame_streams(int elem, size_t bytes) {
-    return elem == 8 || (elem == 4 ? bytes < 48000000 : bytes < 36000000 || bytes >= 500000000);
+constexpr bool frame_streams(int elem, size_t bytes, bool tall) {
+    return elem == 8 || (elem == 4 ? bytes < (tall ? 48000000 : 130000000) : bytes < 36000000 || bytes >= 500000000);
 }
 
 // Blocks of a run in the boundary launches: ring blocks, then frame blocks, each count rounded up

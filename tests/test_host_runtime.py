@@ -184,7 +184,8 @@ def test_frame_stores_stream_in_small_sets(fake):
     or group are few, FP16 again where they are many."""
     _play(fake, """
 streams = lambda: "ELb1E" in [l for l in log() if "k_frame" in l][-1]
-for nx, ny, storage, lattice, want in ((65, 1311, "f32", 9, True), (700, 700, "f32", 9, True), (800, 800, "f32", 9, False), (900, 900, "f64", 9, True),
+for nx, ny, storage, lattice, want in ((65, 1311, "f32", 9, True), (700, 700, "f32", 9, True), (1200, 1200, "f32", 9, True), (1400, 1400, "f32", 9, False),
+                                       (500, 1500, "f32", 9, False), (1500, 500, "f32", 9, True), (900, 900, "f64", 9, True),
                                        (500, 500, "f16", 9, True), (1100, 1100, "f16", 9, False), (1780, 1780, "f16", 37, False),
                                        (1830, 1830, "f16", 37, True), (2000, 300, "f32", 37, False)):
     r = init(run(nx, ny, W=12, bc="nrbc", storage=storage, lattice=lattice))
@@ -192,11 +193,11 @@ for nx, ny, storage, lattice, want in ((65, 1311, "f32", 9, True), (700, 700, "f
     assert streams() == want, (nx, ny, storage)
     r.close()
 g = lbm.Group()
-small = [init(run(200, 200, W=12, bc="nrbc", storage="f32", lattice=9)) for _ in range(16)]
+small = [init(run(200, 200, W=12, bc="nrbc", storage="f32", lattice=9)) for _ in range(40)]
 for k, r in enumerate(small):
     g.add(r)
     g.step(nsteps=1)
-    assert streams() == (k < 13), k
+    assert streams() == (k < 35), k
 """)
 
 
