@@ -137,19 +137,22 @@ constexpr int RING_BLOCK = 64;
 // us, split and not, below and above the line: D2Q37 FP64 340^2 33.7, 37.0, 490^2 (720 blocks) 53.6,
 // 52.4; FP32 490^2 33.5, 37.5, 740^2 (1100) 54.6, 52.1; D2Q17 FP64 490^2 28.0, 29.3, 560^2 (810)
 // 33.1, 32.7; FP32 640^2 24.5, 26.4, 880^2 (1260) 36.7, 37.9.
-// Without characteristic sides no long FP64 chain is shortened, and a state that the L2s hold answers a
-// lone wave soon enough, so there the line is lower the smaller the interior is.  us per step, whole
-// nodes and split, at (blocks, interior nodes / 256): D2Q37 FP32 ZG with 60 cells of layer
-// (608, 38) 17.3, 19.5; channel 52 cells deep (984, 90) 22.5, 25.4; 15 cells (608, 709) 32.1, 32.9; 20
-// cells (488, 474) 26.8, 24.0; 10 cells (536, 1418) 42.4, 37.7; FP16 (608, 38) 17.1, 19.6, (960, 99)
-// 17.9, 21.8; D2Q17 FP64 (456, 91) 14.2, 15.1, (608, 709) 27.3, 25.6, FP32 (688, 969) 19.5, 20.8.  With a
-// ring D2Q37 FP32 (984, 90) 31.6, 25.7, D2Q17 FP16 (1104, 969) 21.1, 19.5, (1184, 241) 18.9, 19.8; FP64
-// D2Q37, whose line is lower already, (456, 91) 24.5, 23.2.
+// Without characteristic sides no long FP64 chain is shortened, and a state that the L2s hold answers
+// a lone wave soon enough, so there the line is lower the smaller the interior is.  us per step, whole
+// nodes and split, at (blocks, interior nodes / 256): D2Q37 FP32 ZG with 60 cells of layer (608, 38)
+// 17.3, 19.5; channel 52 cells deep (984, 90) 22.5, 25.4; 15 cells (608, 709) 32.1, 32.9; 20 cells
+// (488, 474) 26.8, 24.0; 10 cells (536, 1418) 42.4, 37.7; FP16 (608, 38) 17.1, 19.6, (960, 99) 17.9,
+// 21.8; D2Q17 FP64 (456, 91) 14.2, 15.1, (608, 709) 27.3, 25.6, FP32 (688, 969) 19.5, 20.8, FP16 (456,
+// 91) 12.4, 11.8, (608, 709) 15.3, 16.5.  With a ring D2Q37 FP32 (984, 90) 31.6, 25.7, D2Q17 FP16
+// (1104, 969) 21.1, 19.5, (1184, 241) 18.9, 19.8; FP64 D2Q37, whose line is lower already, (456, 91)
+// 24.5, 23.2.  D2Q37 FP32 beside a large interior: (952, 1904) 52.0, 55.2, 832^2 ring (900, 2480)
+// 57.9, 61.1, ZG 57.0, 58.1, (696, 3891) 86.5, 76.8.
 constexpr int SPLIT_BLOCK = 64;
 constexpr int split_most(int q, int elem, bool ring, long long interior) {
-    const int most = 256 * (q == 37 ? (elem == 8 ? 2 : 4) : q == 17 ? (elem == 8 ? 3 : 5) : 0);
+    const int most = 256 * (q == 37 ? (elem == 8 ? 2 : elem == 4 && interior > 256 * 1024 ? 3 : 4)
+                            : q == 17 ? (elem == 8 ? 3 : 5) : 0);
     const long long line = ring                  ? 1024 + interior / 1024
-                           : elem < 8            ? 416 + interior / 1024
+                           : elem < 8            ? (q == 37 ? 416 + interior / 1024 : 448 + interior / 2048)
                            : q == 37             ? most
                                                  : 384 + interior / 512;
     return line < most ? (int)line : most;

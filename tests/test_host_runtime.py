@@ -163,8 +163,10 @@ for nx, ny, bx, by, W, storage, lattice, split in (
         (100, 100, "zg", "zg", 60, "f16", 37, False), (100, 100, "nrbc", "nrbc", 60, "f16", 37, True),
         (156, 1183, "zg", "periodic", 15, "f32", 37, False), (350, 350, "zg", "zg", 20, "f32", 37, True),
         (300, 80, "zg", "zg", 32, "f64", 17, False), (300, 80, "nrbc", "nrbc", 32, "f64", 17, True),
+        (300, 80, "zg", "zg", 32, "f16", 17, True), (156, 1183, "zg", "periodic", 15, "f16", 17, False),
         (300, 80, "zg", "zg", 32, "f64", 37, True), (156, 1183, "zg", "periodic", 15, "f64", 17, True), (500, 500, "zg", "zg", 20, "f32", 17, False),
-        (600, 600, "periodic", "periodic", 0, "f64", 37, True), (100, 100, "zg", "zg", 60, "f32", 9, False)):
+        (600, 600, "periodic", "periodic", 0, "f64", 37, True), (800, 800, "nrbc", "nrbc", 16, "f32", 37, False),
+        (800, 800, "nrbc", "nrbc", 16, "f16", 37, True), (800, 800, "nrbc", "nrbc", 10, "f32", 37, True), (100, 100, "zg", "zg", 60, "f32", 9, False)):
     r = lbm.Run(nx, ny, 0.8, storage=storage, lattice=lattice)
     r.set_bc(3, bx); r.set_bc(12, by)
     if W:
