@@ -192,9 +192,9 @@ lbm_status lbm_node_classes(lbm_handle h, int64_t out[4]);
 /* Bytes of device memory the run needs at its peak (populations, PML Q, moment strips, ring
  * buffers, descriptor, and the larger of the transient staging of the input fields while
  * lbm_init_fields runs and the bands of the two-step passes, for a run that takes them by itself),
- * for admission control.  The bands are a help, not a need: they give way to the staging,
- * a run that finds no memory for them or gives them up to another buffer takes single steps, and a group that takes
- * pairs brings them to its members for as long as they are in it. */
+ * for admission control.  The bands are a help, not a need: they give way to the staging, a run
+ * that finds no memory for them or gives them up to another buffer takes single steps, and a
+ * group that takes pairs brings them to its members for as long as they are in it. */
 lbm_status lbm_footprint(lbm_handle h, size_t *bytes);
 
 /* Allocate device state and set f*(x, 0) = feq(rho, u, T)(x), Q = 0 (Sec. 2 algorithm
